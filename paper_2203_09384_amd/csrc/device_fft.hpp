@@ -173,6 +173,68 @@ __device__ __forceinline__ void dft16(cf (&x)[16])
     }
 }
 
+// cos(2 pi e / 32) and sin(2 pi e / 32) at the odd e of the first quarter;
+// even e are entries e / 2 of the 16-point tables.
+constexpr float kCos32[4] = {0.98078528040323044f, 0.83146961230254524f, 0.55557023301960222f,
+                             0.19509032201612827f};
+
+// a * exp(S 2 pi i E / 32) with E known at compile time.
+template <int S, int E>
+__device__ __forceinline__ cf rot32(cf a)
+{
+    constexpr int e = ((E % 32) + 32) % 32;
+    if constexpr (e % 2 == 0) {
+        return rot16<S, e / 2>(a);
+    } else {
+        // fold into the first quarter: exp(i (q pi / 2 + r)), r = e mod 8
+        constexpr int q = e / 8, r = e % 8;
+        constexpr float cr = kCos32[r / 2], sr = kCos32[3 - r / 2] * (float)S;
+        return rot16<S, 4 * q>(cf{cr * a.x - sr * a.y, cr * a.y + sr * a.x});
+    }
+}
+
+template <int S, int N2>
+__device__ __forceinline__ void rot_row32(cf (&x)[32])
+{
+    x[8 + N2] = rot32<S, N2 * 1>(x[8 + N2]);
+    x[16 + N2] = rot32<S, N2 * 2>(x[16 + N2]);
+    x[24 + N2] = rot32<S, N2 * 3>(x[24 + N2]);
+}
+
+// radix-32 as 4 x 8: n = 8 n1 + n2, k = k1 + 4 k2.
+//   Y[k1][n2] = DFT4 over n1 of x[8 n1 + n2], kept at x[8 k1 + n2]
+//   Y[k1][n2] *= exp(S 2 pi i n2 k1 / 32)
+//   X[k1 + 4 k2] = DFT8 over n2 of Y[k1][n2]
+template <int S>
+__device__ __forceinline__ void dft32(cf (&x)[32])
+{
+#pragma unroll
+    for (int n2 = 0; n2 < 8; n2++)
+        dft4<S>(x[n2], x[8 + n2], x[16 + n2], x[24 + n2]);
+    rot_row32<S, 1>(x);
+    rot_row32<S, 2>(x);
+    rot_row32<S, 3>(x);
+    rot_row32<S, 4>(x);
+    rot_row32<S, 5>(x);
+    rot_row32<S, 6>(x);
+    rot_row32<S, 7>(x);
+    cf y[32];
+#pragma unroll
+    for (int k1 = 0; k1 < 4; k1++) {
+        cf z[8];
+#pragma unroll
+        for (int n2 = 0; n2 < 8; n2++)
+            z[n2] = x[8 * k1 + n2];
+        dft8<S>(z);
+#pragma unroll
+        for (int k2 = 0; k2 < 8; k2++)
+            y[k1 + 4 * k2] = z[k2];
+    }
+#pragma unroll
+    for (int k = 0; k < 32; k++)
+        x[k] = y[k];
+}
+
 // DFT_R on the R values v[Q0 + r * QS], r < R, of a thread's register array.
 template <int R, int S, int QS, int EPT>
 __device__ __forceinline__ void dft_strided(cf (&v)[EPT], int q0)
@@ -187,9 +249,11 @@ __device__ __forceinline__ void dft_strided(cf (&v)[EPT], int q0)
         dft4<S>(x[0], x[1], x[2], x[3]);
     } else if constexpr (R == 8) {
         dft8<S>(x);
-    } else {
-        static_assert(R == 16, "radix must be 2, 4, 8 or 16");
+    } else if constexpr (R == 16) {
         dft16<S>(x);
+    } else {
+        static_assert(R == 32, "radix must be 2, 4, 8, 16 or 32");
+        dft32<S>(x);
     }
 #pragma unroll
     for (int r = 0; r < R; r++)
@@ -208,7 +272,7 @@ struct Sched {
     static constexpr int NP = LOG2N / LOG2EPT + (REM ? 1 : 0);
     static constexpr int log2r(int p) { return idx::sched_log2r(LOG2N, LOG2EPT, p); }
     static constexpr int log2ns(int p) { return idx::sched_log2ns(LOG2N, LOG2EPT, p); }
-    static_assert(LOG2EPT >= 1 && LOG2EPT <= 4, "EPT must be 2..16");
+    static_assert(LOG2EPT >= 1 && LOG2EPT <= 5, "EPT must be 2..32");
     static_assert(LOG2EPT <= LOG2N, "EPT must not exceed N");
 };
 
@@ -632,59 +696,25 @@ __device__ __forceinline__ void run2_prefetch(cf (&v)[1 << E], int t, const cf* 
 }
 
 // run2 over workgroup-wide exchanges that calls slice(P) before pass P,
-// after that pass's twiddle row is read: a caller's loads for its next tile,
-// spread over the passes.  Passes P < K read their rows from `lrows`, a copy
-// in LDS with the row padding PAD (copy_rows_padded, the first K passes'
-// rows); later passes from `grows`, the table itself.  A wait for an LDS
-// row covers none of the slices' global loads; a wait for a global row
-// covers the slices issued before it.
-template <int L, int E, int S, int PAD, int K, int P = 0, class F>
-__device__ __forceinline__ void run2_slices(cf (&v)[1 << E], int t, const cf* lrows, const cf* __restrict__ grows,
-                                            cf* lds, F& slice)
+// after that pass's twiddle row is read: a caller's loads for its next
+// array, spread over the passes.  The rows are a copy in LDS with the row
+// padding PAD (copy_rows_padded): a wait for an LDS row covers none of the
+// slices' global loads.
+template <int L, int E, int S, int PAD, int P = 0, class F>
+__device__ __forceinline__ void run2_slices(cf (&v)[1 << E], int t, const cf* lrows, cf* lds, F& slice)
 {
     using SC = Sched<L, E>;
     cf w[SC::EPT];
-    if constexpr (SC::log2ns(P) > 0) {
-        if constexpr (P < K)
-            load_row<L, E, S, P, PAD>(w, lrows, t);
-        else
-            load_row<L, E, S, P, 0>(w, grows, t);
-    }
+    if constexpr (SC::log2ns(P) > 0)
+        load_row<L, E, S, P, PAD>(w, lrows, t);
     slice(std::integral_constant<int, P>{});
     pass_compute2<L, E, S, P>(v, w);
     if constexpr (P + 1 < SC::NP) {
         if constexpr (P > 0)
             lds_sync<false>();  // all reads of the previous exchange are done
         exchange2<L, E, P, false>(v, t, lds);
-        run2_slices<L, E, S, PAD, K, P + 1>(v, t, lrows, grows, lds, slice);
+        run2_slices<L, E, S, PAD, P + 1>(v, t, lrows, lds, slice);
     }
-}
-
-// Leading passes whose twiddle rows, padded by PAD, fit in `bytes` of LDS.
-template <int L, int E, int PAD>
-__host__ __device__ constexpr int rows_prefix_passes(int bytes)
-{
-    int k = 0;
-    while (k < Sched<L, E>::NP && Layout2<L, E>::rows_offset(k + 1) / (1 << E) * ((1 << E) + PAD) * 8 <= bytes)
-        k++;
-    return k;
-}
-
-// Entries (float2) of the padded LDS copy of the first K passes' rows.
-template <int L, int E, int PAD>
-__host__ __device__ constexpr int padded_rows_prefix(int K)
-{
-    return Layout2<L, E>::rows_offset(K) / (1 << E) * ((1 << E) + PAD);
-}
-
-// Copies the first K passes' rows of `src` to `dst`, padded as above.
-template <int L, int E, int PAD, int K>
-__device__ __forceinline__ void copy_rows_prefix_padded(cf* dst, const cf* __restrict__ src, int tid, int nthreads)
-{
-    static_assert(!idx::rows_entry_major(L), "row-major tables only");
-    constexpr int EPT = 1 << E, TOT = Layout2<L, E>::rows_offset(K);
-    for (int i = tid; i < TOT; i += nthreads)
-        dst[i / EPT * (EPT + PAD) + i % EPT] = src[i];
 }
 
 }  // namespace mifft

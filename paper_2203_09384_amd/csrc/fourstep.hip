@@ -13,14 +13,16 @@
 // so that every global load and store is a run of 16 complex values (one
 // 128-byte line), and transforms them with the same Stockham passes as the
 // batched kernels.  Long inner transforms are read straight into registers
-// (the tile's transform index is the fastest lane index); short ones are
-// staged through LDS so that their exchanges stay inside one wavefront.
+// (the tile's transform index is the fastest lane index; from 512 points up
+// with the passes of wide_tile.hpp); short ones are staged through LDS so
+// that their exchanges stay inside one wavefront.
 // w_N^j is built from a two-level FP32 table (w_N^{1024 a} and w_N^{b},
 // both from FP64 sincospi); the column pass reads it as three levels in LDS.
 #include "device_fft.hpp"
 #include "launch.hpp"
 #include "fourstep.hpp"
 #include "tile_fft.hpp"
+#include "wide_tile.hpp"
 
 namespace mifft {
 namespace {
@@ -47,31 +49,26 @@ __device__ __forceinline__ cf big_twiddle(const cf* __restrict__ lo, const cf* _
 // 2^18, cost a workgroup per CU at 256-point columns.)
 constexpr bool tw3_in_lds(int L) { return L >= 15; }
 
-// Columns per pass-1 tile: 16 (whole 128-byte lines), or 8 for 1024-point
-// columns so that two workgroups fit one CU's LDS (MI355X, 2^26 elements:
-// 2^20 616 -> 578 us, 2^19 583 -> 547 us).
-constexpr int col_tile(int L1) { return L1 >= 10 ? 8 : 16; }
 // Columns of 128+ points load straight into registers (MI355X: 2^15
 // 485 -> 468 us, 2^16 494 -> 479 us against staging 128- and 256-point
 // columns through LDS); the row pass keeps the axis-pass threshold.
 constexpr bool col_direct(int L1) { return L1 >= 7; }
 
-// Pass 1: tile = columns n2 in [T nb, T nb + T) of transform b (T =
-// col_tile).  Long columns (col_direct) are read straight into registers
+// Pass 1, columns of up to 256 points: tile = columns n2 in
+// [16 nb, 16 nb + 16) of transform b.  Long columns (col_direct) are read straight into registers
 // (the column index is the fastest lane index: rows of T values per
 // wavefront access); short ones are staged through LDS so their exchanges
 // stay inside one wavefront.  Either way the outputs go out through LDS:
 // the tile's outputs Y[k1 + N1 n2] form one contiguous block.
 template <int L1, int L2, int S>
-__global__ __launch_bounds__(col_tile(L1)*((1 << L1) >> inner_e(L1))) void k_fourstep1(
+__global__ __launch_bounds__(TILE*((1 << L1) >> inner_e(L1))) void k_fourstep1(
     const cf* __restrict__ in, cf* __restrict__ out, const cf* __restrict__ rows, const cf* __restrict__ tlo,
-    const cf* __restrict__ thi, int64_t ntiles)
+    const cf* __restrict__ thi)
 {
-    constexpr int T = col_tile(L1), LT = T == 16 ? 4 : 3;
+    constexpr int T = TILE, LT = 4;
     constexpr int E = inner_e(L1), N1 = 1 << L1, N2 = 1 << L2;
     constexpr int EPT = 1 << E, TPT = N1 / EPT, WG = T * TPT, ST = stage_stride<L1, E>();
     constexpr bool DIRECT = col_direct(L1);
-    static_assert(T == 16 || DIRECT, "8-column tiles load directly");
     // the three-level table in LDS (tw3_in_lds): twl[c], twl[32 + b],
     // twl[64 + a]
     constexpr bool TW3 = tw3_in_lds(L1 + L2);
@@ -80,14 +77,7 @@ __global__ __launch_bounds__(col_tile(L1)*((1 << L1) >> inner_e(L1))) void k_fou
     __shared__ cf lds[T * ST];
     __shared__ cf twl[NTW];
     const int tid = threadIdx.x;
-    int64_t tile = blockIdx.x;
-    if constexpr (T < 16) {
-        // tiles 2i and 2i+1 share 128-byte lines: same XCD (blocks b, b + 8)
-        const int64_t g = blockIdx.x;
-        tile = idx::xcd_group_tile(g, 2);
-    }
-    if (tile >= ntiles)
-        return;
+    const int64_t tile = blockIdx.x;
     const int nb = (int)(tile % (N2 / T));
     // thread (tb, t): transform tb of the tile, thread t of that transform
     const int tb = DIRECT ? (tid & (T - 1)) : tid / TPT;
@@ -152,6 +142,90 @@ __global__ __launch_bounds__(col_tile(L1)*((1 << L1) >> inner_e(L1))) void k_fou
     }
 }
 
+// Pass 1 for columns of 512 and more points: 16-column tiles with 32 points
+// per thread.  The outputs leave through LDS too, one float plane
+// at a time: column c at c (N1 + 4), which puts the 16 columns of a wavefront's
+// writes 4 banks apart and each column's 4 points between them.
+template <int L1, int L2, int S>
+__global__ __launch_bounds__(Wide<L1>::WG, WIDE_WAVES) void k_fourstep1_wide(
+    const cf* __restrict__ in, cf* __restrict__ out, const cf* __restrict__ rows, const cf* __restrict__ tlo,
+    const cf* __restrict__ thi)
+{
+    using W = Wide<L1>;
+    constexpr int N1 = 1 << L1, N2 = 1 << L2, T = WIDE_TILE, WG = W::WG, TPT = W::TPT;
+    constexpr int NTW = 64 + ((1 << (L1 + L2)) >> 10), CS = N1 + 4;
+    static_assert(T * CS <= W::PLANE, "the output planes fit the exchange plane");
+    __shared__ float lds[W::PLANE];
+    __shared__ cf twl[NTW];
+    const int tid = threadIdx.x, c = tid & (T - 1), t = tid / T;
+    const int64_t tile = blockIdx.x;
+    const int nb = (int)(tile % (N2 / T));
+    cf v[32];
+    {
+        const char* p = reinterpret_cast<const char*>(in + idx::fourstep_col_in(tile, c, t, L1, L2, T));
+#pragma unroll
+        for (int m = 0; m < 32; m++)
+            v[m] = ld_data<false>(p + (int64_t)m * (TPT * N2 * 8));
+    }
+    for (int i = tid; i < NTW; i += WG)
+        twl[i] = i < 32 ? tlo[i] : i < 64 ? tlo[32 * (i - 32)] : thi[i - 64];
+    cf w4[4];
+    wide_run<L1, S>(v, t, rows, lds + c, w4);
+    const unsigned n2 = nb * T + c;
+#pragma unroll
+    for (int m = 0; m < 32; m++) {
+        const unsigned j = n2 * (t + m * TPT);
+        cf w = cmul(cmul(twl[64 + (j >> 10)], twl[32 + ((j >> 5) & 31u)]), twl[j & 31u]);
+        if constexpr (S > 0)
+            w.y = -w.y;
+        v[m] = cmul(v[m], w);
+    }
+    // The tile's outputs Y[k1 + N1 n2] are one block: thread tid takes its
+    // pairs 2 (tid + i WG), + 1.
+    float x[32];
+    float* my = lds + c * CS + t;
+    const float* blk = lds;
+    __syncthreads();  // the last exchange is read
+#pragma unroll
+    for (int m = 0; m < 32; m++)
+        my[m * TPT] = v[m].x;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        const int e = 2 * (tid + i * WG);
+        const float* q = blk + (e / N1) * CS + e % N1;
+        x[2 * i] = q[0];
+        x[2 * i + 1] = q[1];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < 32; m++)
+        my[m * TPT] = v[m].y;
+    __syncthreads();
+    gv4* dst = reinterpret_cast<gv4*>(out + tile * (T * N1)) + tid;
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        const int e = 2 * (tid + i * WG);
+        const float* q = blk + (e / N1) * CS + e % N1;
+        gv4 o;
+        o.x = x[2 * i];
+        o.y = q[0];
+        o.z = x[2 * i + 1];
+        o.w = q[1];
+        dst[i * WG] = o;
+    }
+}
+
+// Pass 2 with rows of 512 and more points.
+template <int L1, int L2, int S>
+__global__ __launch_bounds__(Wide<L2>::WG, WIDE_WAVES) void k_fourstep2_wide(cf* __restrict__ io,
+                                                                            const cf* __restrict__ rows,
+                                                                            int64_t count, float scale)
+{
+    __shared__ float lds[Wide<L2>::PLANE];
+    wide_axis_tile<L2, S>(io, rows, lds, (int64_t)blockIdx.x * WIDE_TILE, count, L1, scale);
+}
+
 // Pass 2 (in place): tile = rows k1 in [16 kb, 16 kb + 16) of transform b,
 // elements Y[k1 + N1 n2] (stride N1 along n2); outputs X[k1 + N1 k2] at the
 // same addresses: the axis pass of a multidimensional transform with
@@ -160,50 +234,59 @@ template <int L1, int L2, int S>
 __global__ __launch_bounds__(axis_wg<L2>()) void k_fourstep2(cf* __restrict__ io, const cf* __restrict__ rows,
                                                             int64_t count, float scale)
 {
-    static_assert(axis_tile(L2) == TILE, "row tiles of 16");
+    static_assert(AXIS_TILE == TILE, "row tiles of 16");
     __shared__ cf lds[TILE * stage_stride<L2, axis_e(L2)>()];
     const int64_t q0 = (int64_t)blockIdx.x * TILE;
-    if constexpr (axis_direct(L2))
-        axis_tile_direct<L2, S>(io, rows, lds, q0, count, L1, scale);
-    else
-        axis_tile_staged<L2, S>(io, rows, lds, q0, count, L1, scale);
+    axis_tile_staged<L2, S>(io, rows, lds, q0, count, L1, scale);
 }
 
 template <int L1, int L2, int S>
 hipError_t launch_fourstep(const void* in, void* out, const void* rows1, const void* rows2, const void* tlo,
                            const void* thi, int64_t batch, float scale, hipStream_t stream)
 {
-    constexpr int T1 = col_tile(L1);
-    constexpr int WG1 = T1 * ((1 << L1) >> inner_e(L1));
-    constexpr int WG2 = TILE * ((1 << L2) >> inner_e(L2));
-    const int64_t t1 = batch * ((1 << L2) / T1), g2 = batch * ((1 << L1) / TILE);
-    const int64_t g1 = T1 < 16 ? (t1 + 15) & ~int64_t(15) : t1;  // whole chunks for the XCD pairing
-    const hipError_t e = launch_kernel((k_fourstep1<L1, L2, S>), dim3((unsigned)g1), dim3(WG1), 0, stream,
-                                       static_cast<const cf*>(in), static_cast<cf*>(out),
-                                       static_cast<const cf*>(rows1), static_cast<const cf*>(tlo),
-                                       static_cast<const cf*>(thi), t1);
+    const int64_t t1 = batch * ((1 << L2) / TILE), t2 = batch * ((1 << L1) / TILE);
+    const cf *src = static_cast<const cf*>(in), *lo = static_cast<const cf*>(tlo), *hi = static_cast<const cf*>(thi);
+    const cf *r1 = static_cast<const cf*>(rows1), *r2 = static_cast<const cf*>(rows2);
+    cf* dst = static_cast<cf*>(out);
+    hipError_t e;
+    if constexpr (wide_len(L1))
+        e = launch_kernel((k_fourstep1_wide<L1, L2, S>), dim3((unsigned)t1), dim3(Wide<L1>::WG), 0, stream, src, dst,
+                          r1, lo, hi);
+    else
+        e = launch_kernel((k_fourstep1<L1, L2, S>), dim3((unsigned)t1), dim3(TILE * ((1 << L1) >> inner_e(L1))), 0,
+                          stream, src, dst, r1, lo, hi);
     if (e != hipSuccess)
         return e;
-    // pass 2 is the axis pass of stride N1 over batch N1 transforms: the
-    // persistent form where it applies (1024-point rows)
-    hipError_t e2;
-    if (launch_axis_persistent<L2, S>(out, rows2, batch << L1, L1, scale, stream, &e2))
-        return e2;
-    return launch_kernel((k_fourstep2<L1, L2, S>), dim3((unsigned)g2), dim3(WG2), 0, stream, static_cast<cf*>(out),
-                       static_cast<const cf*>(rows2), batch << L1, scale);
+    // pass 2 is the axis pass of stride N1 over batch N1 transforms
+    if constexpr (wide_len(L2))
+        return launch_kernel((k_fourstep2_wide<L1, L2, S>), dim3((unsigned)t2), dim3(Wide<L2>::WG), 0, stream, dst,
+                             r2, batch << L1, scale);
+    else
+        return launch_kernel((k_fourstep2<L1, L2, S>), dim3((unsigned)t2), dim3(axis_wg<L2>()), 0, stream, dst, r2,
+                             batch << L1, scale);
+}
+
+// log2 of the points per thread, and the LDS bytes, of an inner transform.
+constexpr int fs_e(int Li) { return wide_len(Li) ? WIDE_E : inner_e(Li); }
+
+template <int Li>
+constexpr int fs_lds()
+{
+    if constexpr (wide_len(Li))
+        return Wide<Li>::PLANE * (int)sizeof(float);
+    else
+        return TILE * stage_stride<Li, inner_e(Li)>() * (int)sizeof(cf);
 }
 
 template <int L>
 void add_len()
 {
     constexpr int L1 = (L + 1) / 2, L2 = L / 2;
-    const FourStep fs{L, L1, L2, inner_e(L1), inner_e(L2), Layout2<L1, inner_e(L1)>::rows_total(),
-                      Layout2<L2, inner_e(L2)>::rows_total(), &launch_fourstep<L1, L2, -1>,
-                      &launch_fourstep<L1, L2, +1>,
-                      (int)((col_tile(L1) * stage_stride<L1, inner_e(L1)>() +
-                             (tw3_in_lds(L) ? 64 + (1 << (L - 10)) : 0)) *
-                            sizeof(cf)),
-                      (int)(TILE * stage_stride<L2, inner_e(L2)>() * sizeof(cf)), col_tile(L1)};
+    constexpr int E1 = fs_e(L1), E2 = fs_e(L2);
+    const int tw = tw3_in_lds(L) ? (64 + (1 << (L - 10))) * (int)sizeof(cf) : 0;
+    const FourStep fs{L, L1, L2, E1, E2, Layout2<L1, E1>::rows_total(), Layout2<L2, E2>::rows_total(),
+                      &launch_fourstep<L1, L2, -1>, &launch_fourstep<L1, L2, +1>, fs_lds<L1>() + tw, fs_lds<L2>(),
+                      TILE};
     register_fourstep(fs);
 }
 

@@ -6,14 +6,14 @@
 // Eq. (dft) applied along each axis in turn.  The last (contiguous) axis
 // runs through the batched 1D kernels; every other axis runs here: a
 // transform along an axis of stride s has its points s elements apart, and
-// a workgroup takes a tile of TILE transforms adjacent in memory, so that
-// row n of the tile is TILE consecutive complex values (one 128-byte line
-// when TILE = 16).  Each transform runs the Stockham passes with its own
+// a workgroup takes a tile of 16 transforms adjacent in memory, so that
+// row n of the tile is 16 consecutive complex values (one 128-byte line).  Each transform runs the Stockham passes with its own
 // LDS region, and the result is written over the input.
 #include "device_fft.hpp"
 #include "launch.hpp"
 #include "nd.hpp"
 #include "tile_fft.hpp"
+#include "wide_tile.hpp"
 
 namespace mifft {
 namespace {
@@ -22,48 +22,44 @@ template <int L, int S>
 __global__ __launch_bounds__(axis_wg<L>()) void k_axis(cf* __restrict__ io, const cf* __restrict__ rows,
                                                         int64_t count, int log2s, float scale)
 {
-    constexpr int TILE = axis_tile(L);
-    __shared__ cf lds[TILE * stage_stride<L, axis_e(L)>()];
-    int64_t tile = blockIdx.x;
-    if constexpr (TILE < 16) {
-        // The G = 16 / TILE tiles G i .. G i + G-1 share 128-byte lines (when
-        // the stride is >= 16): run them on the same XCD (blocks b, b + 8,
-        // ... of a chunk of 8 G blocks).
-        constexpr int G = 16 / TILE;
-        const int64_t b = blockIdx.x;
-        tile = idx::xcd_group_tile(b, G);
-    }
-    const int64_t q0 = tile * TILE;
-    if (q0 >= count)
-        return;
-    if constexpr (axis_direct(L))
-        axis_tile_direct<L, S>(io, rows, lds, q0, count, log2s, scale);
-    else
-        axis_tile_staged<L, S>(io, rows, lds, q0, count, log2s, scale);
+    __shared__ cf lds[AXIS_TILE * stage_stride<L, axis_e(L)>()];
+    axis_tile_staged<L, S>(io, rows, lds, (int64_t)blockIdx.x * AXIS_TILE, count, log2s, scale);
+}
+
+// 512 points and more: 32 points per thread.
+template <int L, int S>
+__global__ __launch_bounds__(Wide<L>::WG, WIDE_WAVES) void k_axis_wide(cf* __restrict__ io,
+                                                                      const cf* __restrict__ rows, int64_t count,
+                                                                      int log2s, float scale)
+{
+    __shared__ float lds[Wide<L>::PLANE];
+    wide_axis_tile<L, S>(io, rows, lds, (int64_t)blockIdx.x * WIDE_TILE, count, log2s, scale);
 }
 
 template <int L, int S>
 hipError_t launch_axis(void* io, const void* rows, int64_t count, int log2s, float scale, hipStream_t stream)
 {
-    constexpr int TILE = axis_tile(L);
-    hipError_t e;
-    if (launch_axis_persistent<L, S>(io, rows, count, log2s, scale, stream, &e))
-        return e;
-    int64_t grid = (count + TILE - 1) / TILE;
-    if (TILE < 16)
-        grid = (grid + 127) & ~int64_t(127);  // whole chunks for the XCD grouping
-    return launch_kernel((k_axis<L, S>), dim3((unsigned)grid), dim3(axis_wg<L>()), 0, stream, static_cast<cf*>(io),
-                       static_cast<const cf*>(rows), count, log2s, scale);
+    const dim3 grid((unsigned)((count + AXIS_TILE - 1) / AXIS_TILE));
+    if constexpr (wide_len(L))
+        return launch_kernel((k_axis_wide<L, S>), grid, dim3(Wide<L>::WG), 0, stream, static_cast<cf*>(io),
+                             static_cast<const cf*>(rows), count, log2s, scale);
+    else
+        return launch_kernel((k_axis<L, S>), grid, dim3(axis_wg<L>()), 0, stream, static_cast<cf*>(io),
+                             static_cast<const cf*>(rows), count, log2s, scale);
 }
 
 template <int L>
 void add_axis()
 {
-    constexpr int E = axis_e(L);
+    constexpr int E = wide_len(L) ? WIDE_E : axis_e(L);
     const int rows = ((1 << L) >> E) > 1 ? Layout2<L, E>::rows_total() : 0;
-    const int lds = (int)(axis_tile(L) * stage_stride<L, E>() * sizeof(cf));
-    register_axis(KernelAxis{L, E, -1, axis_tile(L), &launch_axis<L, -1>, rows, lds});
-    register_axis(KernelAxis{L, E, +1, axis_tile(L), &launch_axis<L, +1>, rows, lds});
+    int lds;
+    if constexpr (wide_len(L))
+        lds = Wide<L>::PLANE * (int)sizeof(float);
+    else
+        lds = AXIS_TILE * stage_stride<L, E>() * (int)sizeof(cf);
+    register_axis(KernelAxis{L, E, -1, AXIS_TILE, &launch_axis<L, -1>, rows, lds});
+    register_axis(KernelAxis{L, E, +1, AXIS_TILE, &launch_axis<L, +1>, rows, lds});
 }
 
 struct AxisRegistrar {
