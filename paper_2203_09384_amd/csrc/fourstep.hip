@@ -21,6 +21,7 @@
 #include "device_fft.hpp"
 #include "launch.hpp"
 #include "fourstep.hpp"
+#include "stream.hpp"
 #include "tile_fft.hpp"
 #include "wide_tile.hpp"
 
@@ -60,7 +61,7 @@ constexpr bool col_direct(int L1) { return L1 >= 7; }
 // wavefront access); short ones are staged through LDS so their exchanges
 // stay inside one wavefront.  Either way the outputs go out through LDS:
 // the tile's outputs Y[k1 + N1 n2] form one contiguous block.
-template <int L1, int L2, int S>
+template <int L1, int L2, int S, bool NT>
 __global__ __launch_bounds__(TILE*((1 << L1) >> inner_e(L1))) void k_fourstep1(
     const cf* __restrict__ in, cf* __restrict__ out, const cf* __restrict__ rows, const cf* __restrict__ tlo,
     const cf* __restrict__ thi)
@@ -87,7 +88,8 @@ __global__ __launch_bounds__(TILE*((1 << L1) >> inner_e(L1))) void k_fourstep1(
     if constexpr (DIRECT) {
 #pragma unroll
         for (int m = 0; m < EPT; m++)
-            v[m] = ld_c(in + idx::fourstep_col_in(tile, tb, t + m * TPT, L1, L2, T));
+            v[m] = ld_data<NT>(
+                reinterpret_cast<const char*>(in + idx::fourstep_col_in(tile, tb, t + m * TPT, L1, L2, T)));
     } else {
         // stage: 16 consecutive columns per row n1 (one 128-byte line)
 #pragma unroll
@@ -146,7 +148,7 @@ __global__ __launch_bounds__(TILE*((1 << L1) >> inner_e(L1))) void k_fourstep1(
 // per thread.  The outputs leave through LDS too, one float plane
 // at a time: column c at c (N1 + 4), which puts the 16 columns of a wavefront's
 // writes 4 banks apart and each column's 4 points between them.
-template <int L1, int L2, int S>
+template <int L1, int L2, int S, bool NT>
 __global__ __launch_bounds__(Wide<L1>::WG, WIDE_WAVES) void k_fourstep1_wide(
     const cf* __restrict__ in, cf* __restrict__ out, const cf* __restrict__ rows, const cf* __restrict__ tlo,
     const cf* __restrict__ thi)
@@ -165,7 +167,7 @@ __global__ __launch_bounds__(Wide<L1>::WG, WIDE_WAVES) void k_fourstep1_wide(
         const char* p = reinterpret_cast<const char*>(in + idx::fourstep_col_in(tile, c, t, L1, L2, T));
 #pragma unroll
         for (int m = 0; m < 32; m++)
-            v[m] = ld_data<false>(p + (int64_t)m * (TPT * N2 * 8));
+            v[m] = ld_data<NT>(p + (int64_t)m * (TPT * N2 * 8));
     }
     for (int i = tid; i < NTW; i += WG)
         twl[i] = i < 32 ? tlo[i] : i < 64 ? tlo[32 * (i - 32)] : thi[i - 64];
@@ -217,53 +219,78 @@ __global__ __launch_bounds__(Wide<L1>::WG, WIDE_WAVES) void k_fourstep1_wide(
 }
 
 // Pass 2 with rows of 512 and more points.
-template <int L1, int L2, int S>
+template <int L1, int L2, int S, bool NT>
 __global__ __launch_bounds__(Wide<L2>::WG, WIDE_WAVES) void k_fourstep2_wide(cf* __restrict__ io,
                                                                             const cf* __restrict__ rows,
                                                                             int64_t count, float scale)
 {
     __shared__ float lds[Wide<L2>::PLANE];
-    wide_axis_tile<L2, S>(io, rows, lds, (int64_t)blockIdx.x * WIDE_TILE, count, L1, scale);
+    wide_axis_tile<L2, S, NT>(io, rows, lds, (int64_t)blockIdx.x * WIDE_TILE, count, L1, scale);
 }
 
 // Pass 2 (in place): tile = rows k1 in [16 kb, 16 kb + 16) of transform b,
 // elements Y[k1 + N1 n2] (stride N1 along n2); outputs X[k1 + N1 k2] at the
 // same addresses: the axis pass of a multidimensional transform with
 // stride N1 over batch * N1 transforms.
-template <int L1, int L2, int S>
+template <int L1, int L2, int S, bool NT>
 __global__ __launch_bounds__(axis_wg<L2>()) void k_fourstep2(cf* __restrict__ io, const cf* __restrict__ rows,
                                                             int64_t count, float scale)
 {
     static_assert(AXIS_TILE == TILE, "row tiles of 16");
     __shared__ cf lds[TILE * stage_stride<L2, axis_e(L2)>()];
     const int64_t q0 = (int64_t)blockIdx.x * TILE;
-    axis_tile_staged<L2, S>(io, rows, lds, q0, count, L1, scale);
+    axis_tile_staged<L2, S, NT>(io, rows, lds, q0, count, L1, scale);
 }
 
-template <int L1, int L2, int S>
-hipError_t launch_fourstep(const void* in, void* out, const void* rows1, const void* rows2, const void* tlo,
-                           const void* thi, int64_t batch, float scale, hipStream_t stream)
+// Both passes over `batch` transforms.  NT: the column pass reads and the
+// row pass reads and writes nontemporally; the column pass stores plainly.
+template <int L1, int L2, int S, bool NT>
+hipError_t launch_passes(const cf* in, cf* out, const cf* rows1, const cf* rows2, const cf* tlo, const cf* thi,
+                         int64_t batch, float scale, hipStream_t stream)
 {
     const int64_t t1 = batch * ((1 << L2) / TILE), t2 = batch * ((1 << L1) / TILE);
-    const cf *src = static_cast<const cf*>(in), *lo = static_cast<const cf*>(tlo), *hi = static_cast<const cf*>(thi);
-    const cf *r1 = static_cast<const cf*>(rows1), *r2 = static_cast<const cf*>(rows2);
-    cf* dst = static_cast<cf*>(out);
     hipError_t e;
     if constexpr (wide_len(L1))
-        e = launch_kernel((k_fourstep1_wide<L1, L2, S>), dim3((unsigned)t1), dim3(Wide<L1>::WG), 0, stream, src, dst,
-                          r1, lo, hi);
+        e = launch_kernel((k_fourstep1_wide<L1, L2, S, NT>), dim3((unsigned)t1), dim3(Wide<L1>::WG), 0, stream, in,
+                          out, rows1, tlo, thi);
     else
-        e = launch_kernel((k_fourstep1<L1, L2, S>), dim3((unsigned)t1), dim3(TILE * ((1 << L1) >> inner_e(L1))), 0,
-                          stream, src, dst, r1, lo, hi);
+        e = launch_kernel((k_fourstep1<L1, L2, S, NT>), dim3((unsigned)t1), dim3(TILE * ((1 << L1) >> inner_e(L1))),
+                          0, stream, in, out, rows1, tlo, thi);
     if (e != hipSuccess)
         return e;
     // pass 2 is the axis pass of stride N1 over batch N1 transforms
     if constexpr (wide_len(L2))
-        return launch_kernel((k_fourstep2_wide<L1, L2, S>), dim3((unsigned)t2), dim3(Wide<L2>::WG), 0, stream, dst,
-                             r2, batch << L1, scale);
+        return launch_kernel((k_fourstep2_wide<L1, L2, S, NT>), dim3((unsigned)t2), dim3(Wide<L2>::WG), 0, stream,
+                             out, rows2, batch << L1, scale);
     else
-        return launch_kernel((k_fourstep2<L1, L2, S>), dim3((unsigned)t2), dim3(axis_wg<L2>()), 0, stream, dst, r2,
-                             batch << L1, scale);
+        return launch_kernel((k_fourstep2<L1, L2, S, NT>), dim3((unsigned)t2), dim3(axis_wg<L2>()), 0, stream, out,
+                             rows2, batch << L1, scale);
+}
+
+// Streams run chunk by chunk (stream.hpp): the row pass reads what the
+// column pass left in the memory-side cache.  MI355X at 512 MiB, whole batch
+// and plain accesses -> this: 2^15 427 -> 351 us, 2^16 437 -> 350, 2^17
+// 438 -> 349, 2^18 444 -> 348, 2^19 448 -> 366, 2^20 446 -> 377; at 256 MiB 2^16
+// 221 -> 176 (nontemporal accesses alone).
+template <int L1, int L2, int S>
+hipError_t launch_fourstep(const void* in, void* out, const void* rows1, const void* rows2, const void* tlo,
+                           const void* thi, int64_t batch, float scale, hipStream_t stream)
+{
+    const cf *src = static_cast<const cf*>(in), *lo = static_cast<const cf*>(tlo), *hi = static_cast<const cf*>(thi);
+    const cf *r1 = static_cast<const cf*>(rows1), *r2 = static_cast<const cf*>(rows2);
+    cf* dst = static_cast<cf*>(out);
+    constexpr int64_t EACH = int64_t(sizeof(cf)) << (L1 + L2);
+    if (!is_stream(batch * EACH))
+        return launch_passes<L1, L2, S, false>(src, dst, r1, r2, lo, hi, batch, scale, stream);
+    const int64_t per = chunk_units(EACH);
+    for (int64_t b = 0; b < batch; b += per) {
+        const int64_t nb = batch - b < per ? batch - b : per;
+        const hipError_t e = launch_passes<L1, L2, S, true>(src + (b << (L1 + L2)), dst + (b << (L1 + L2)), r1, r2,
+                                                            lo, hi, nb, scale, stream);
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
 }
 
 // log2 of the points per thread, and the LDS bytes, of an inner transform.

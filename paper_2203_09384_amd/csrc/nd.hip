@@ -23,7 +23,7 @@ __global__ __launch_bounds__(axis_wg<L>()) void k_axis(cf* __restrict__ io, cons
                                                         int64_t count, int log2s, float scale)
 {
     __shared__ cf lds[AXIS_TILE * stage_stride<L, axis_e(L)>()];
-    axis_tile_staged<L, S>(io, rows, lds, (int64_t)blockIdx.x * AXIS_TILE, count, log2s, scale);
+    axis_tile_staged<L, S, false>(io, rows, lds, (int64_t)blockIdx.x * AXIS_TILE, count, log2s, scale);
 }
 
 // 512 points and more: 32 points per thread.
@@ -33,7 +33,7 @@ __global__ __launch_bounds__(Wide<L>::WG, WIDE_WAVES) void k_axis_wide(cf* __res
                                                                       int log2s, float scale)
 {
     __shared__ float lds[Wide<L>::PLANE];
-    wide_axis_tile<L, S>(io, rows, lds, (int64_t)blockIdx.x * WIDE_TILE, count, log2s, scale);
+    wide_axis_tile<L, S, false>(io, rows, lds, (int64_t)blockIdx.x * WIDE_TILE, count, log2s, scale);
 }
 
 template <int L, int S>

@@ -1,0 +1,33 @@
+// How passes over memory use MI355X's 256 MiB memory-side cache.
+//
+// Nontemporal accesses leave the cache to other data; plain ones fill it.
+// Two rules, on the bytes that one direction of a call moves:
+//
+// - Streams.  A call whose input and output together exceed the cache can
+//   find its input there only by accident, and filling it with data that is
+//   not read again costs more than it gives: nontemporal accesses.  A
+//   smaller call reads what the kernel before it has just written, and the
+//   next one reads its output, at the cache's rate: plain accesses.
+//   Measured with 16-column tile copies: 2 x 64 MiB, repeated on the same
+//   buffers, 17 us plain against 23 nontemporal; 2 x 512 MiB 205 against 189.
+// - Chunks.  A transform of several passes over memory runs all its passes
+//   on one chunk of the batch before the next, so that a later pass reads
+//   what the earlier one left in the cache: the first pass reads its input
+//   nontemporally and stores plainly.  256 MiB per chunk measured best
+//   (four-step 2^16 at 512 MiB: one chunk 386 us, 256 MiB 349, 128 MiB 382):
+//   smaller chunks pay more launches, each with its own ramp and drain.
+#pragma once
+#include <stdint.h>
+
+namespace mifft {
+
+constexpr int64_t kStreamBytes = int64_t(128) << 20;
+constexpr int64_t kChunkBytes = int64_t(256) << 20;
+
+// Whether a call that reads `bytes` and writes about as much is a stream.
+inline bool is_stream(int64_t bytes) { return bytes > kStreamBytes; }
+
+// Units of `each` bytes in one chunk.
+inline int64_t chunk_units(int64_t each) { return each >= kChunkBytes ? 1 : kChunkBytes / each; }
+
+}  // namespace mifft

@@ -55,8 +55,8 @@ __device__ __forceinline__ void unit_rows(TwRegs<L, E>& tws)
 // Transforms of up to 256 points (longer ones: wide_tile.hpp): the tile is
 // staged through LDS (rows of TILE values in, one transform per TPT
 // consecutive threads), so each transform's exchanges stay inside one
-// wavefront; staged back the same way.
-template <int L, int S>
+// wavefront; staged back the same way, nontemporally if NT.
+template <int L, int S, bool NT>
 __device__ __forceinline__ void axis_tile_staged(cf* __restrict__ io, const cf* __restrict__ rows, cf* lds,
                                                  int64_t q0, int64_t count, int log2s, float scale)
 {
@@ -71,7 +71,7 @@ __device__ __forceinline__ void axis_tile_staged(cf* __restrict__ io, const cf* 
         const int idx = tid + i * WG;
         const int c = idx & (TILE - 1), n = idx >> LT;
         if (q0 + c < count)
-            lds[c * ST + n] = ld_c(io + addr(c, n));
+            lds[c * ST + n] = ld_data<NT>(reinterpret_cast<const char*>(io + addr(c, n)));
     }
     __syncthreads();
     const int tb = tid / TPT, t = tid % TPT;
@@ -94,7 +94,7 @@ __device__ __forceinline__ void axis_tile_staged(cf* __restrict__ io, const cf* 
         const int idx = tid + i * WG;
         const int c = idx & (TILE - 1), n = idx >> LT;
         if (q0 + c < count)
-            st_c(io + addr(c, n), lds[c * ST + n]);
+            st_data<NT>(reinterpret_cast<char*>(io + addr(c, n)), lds[c * ST + n]);
     }
 }
 

@@ -154,8 +154,9 @@ __device__ __forceinline__ void wide_run(cf (&v)[32], int t, const cf* __restric
 
 // Axis pass over transforms q0 .. q0 + 15 below `count`, in place: a thread
 // loads and stores its points straight from and to HBM, at the same
-// addresses.  Transforms past the end read transform q0 and store nothing.
-template <int L, int S>
+// addresses, nontemporally if NT.  Transforms past the end read transform q0
+// and store nothing.
+template <int L, int S, bool NT>
 __device__ __forceinline__ void wide_axis_tile(cf* __restrict__ io, const cf* __restrict__ rows, float* lds,
                                                int64_t q0, int64_t count, int log2s, float scale)
 {
@@ -168,7 +169,7 @@ __device__ __forceinline__ void wide_axis_tile(cf* __restrict__ io, const cf* __
     cf v[32];
 #pragma unroll
     for (int m = 0; m < 32; m++)
-        v[m] = ld_data<false>(p + m * step);
+        v[m] = ld_data<NT>(p + m * step);
     cf w[4];
     wide_run<L, S>(v, t, rows, lds + c, w);
     // The stores' addresses are computed again: kept from the loads, the 32
@@ -177,7 +178,7 @@ __device__ __forceinline__ void wide_axis_tile(cf* __restrict__ io, const cf* __
     if (live) {
 #pragma unroll
         for (int m = 0; m < 32; m++)
-            st_data<false>(p + m * step, cscale(v[m], scale));
+            st_data<NT>(p + m * step, cscale(v[m], scale));
     }
 }
 

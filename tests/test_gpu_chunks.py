@@ -1,0 +1,33 @@
+"""Transforms of several passes over batches large enough to run chunk by
+chunk: transforms at both ends of a chunk and in a short last one, against
+the FP64 oracle.  Bar, as for every FP32 transform: relative L2 <= 1e-5."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2203_09384_amd import api
+from gpu_util import need_gpu, per_transform_relerr, to_cpu
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-5
+CHUNK = 256 << 20  # bytes
+
+
+def signal(*shape):
+    g = torch.Generator(device="cuda").manual_seed(77)
+    return torch.view_as_complex(torch.rand(shape + (2,), generator=g, device="cuda").mul_(2).sub_(1))
+
+
+@pytest.mark.parametrize("L", [15, 16, 17, 18, 20])
+@pytest.mark.parametrize("sign", [-1, 1])
+def test_four_step_chunks(L, sign):
+    n = 1 << L
+    per = CHUNK // (8 * n)
+    batch = per + 3
+    x = signal(batch, n)
+    print(f"[case] four-step chunks n={n} batch={batch} sign={sign}", flush=True)
+    y = api.Plan(n, batch, sign).execute(x)
+    at = torch.tensor([0, per - 1, per, batch - 1], device="cuda")
+    xs = to_cpu(x[at]).astype(np.complex128)
+    assert per_transform_relerr(to_cpu(y[at]), oracle.forward(xs) if sign < 0 else oracle.inverse(xs)) <= TOL
