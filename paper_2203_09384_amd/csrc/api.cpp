@@ -26,6 +26,7 @@
 #include "ragged.hpp"
 #include "real.hpp"
 #include "registry.hpp"
+#include "stream.hpp"
 
 namespace mifft {
 hipError_t launch_twiddle_2048(void* tw, hipStream_t stream);
@@ -182,32 +183,6 @@ const KernelC32* c32_at(int i) { return (i >= 0 && i < count_c32()) ? &c32_reg()
 
 // ------------------------------------------------------------------ tuning
 namespace {
-struct Variant {
-    int log2ept, wg, kind;
-};
-
-// Built-in choice per log2 N (index 1..11) for FP32: the autotuner's pick on
-// MI355X at 2^26 elements per launch (log2 EPT, workgroup size, variant).
-const Variant kDefaultC32[21] = {
-    {0, 0, 0},     // unused
-    {1, 64, 11},   // N=2     one thread per transform, block staged through LDS
-    {2, 128, 11},  // N=4
-    {3, 64, 11},   // N=8
-    {4, 128, 11},  // N=16
-    {3, 64, 12},   // N=32    several threads per transform, block staged through LDS
-    {3, 256, 12},  // N=64
-    {3, 64, 12},   // N=128
-    {4, 128, 12},  // N=256
-    {3, 64, 12},   // N=512
-    {4, 64, 3},    // N=1024  persistent, next-group prefetch
-    {4, 128, 3},   // N=2048  persistent, next-group prefetch
-    {3, 512, 3},   // N=2^12  one transform per workgroup
-    {4, 512, 3},   // N=2^13
-    {4, 1024, 2},  // N=2^14  135 KiB LDS
-    {0, 0, 9},     // N=2^15 .. 2^20: four-step (column + row pass)
-    {0, 0, 9}, {0, 0, 9}, {0, 0, 9}, {0, 0, 9}, {0, 0, 9},
-};
-
 // Real-input transforms (FFT_R32), per log2 of the half length M = n/2
 // (index 0..14): the half-length transform's configuration, the
 // autotuner's pick on MI355X (R2C + C2R over 2^27 reals).
@@ -372,7 +347,6 @@ struct mifft_plan_s {
     const KernelAxis* ax_opp[2] = {nullptr, nullptr};   // the adjoint's sign
     void* ax_rows[2] = {nullptr, nullptr};
     int ax_log2s[2] = {0, 0};
-    int64_t ax_count[2] = {0, 0};
     float ax_scale[2] = {1.f, 1.f};
     int ax_first = -1;  // the axis passes run for axes ax_first .. 0
     // single-pass 2D (the array fits one workgroup's LDS): no sub-plan
@@ -1142,7 +1116,6 @@ fft_plan create_nd(int rank, const int64_t* dims, int64_t batch, int sign, int d
         p->ax_same[a] = find_axis(L, sign);
         p->ax_opp[a] = find_axis(L, -sign);
         p->ax_log2s[a] = log2s;
-        p->ax_count[a] = batch * (n / dims[a]);
         p->ax_scale[a] = sign > 0 ? 1.0f / (float)dims[a] : 1.0f;
         log2s += L;
         const KernelAxis* k = p->ax_same[a];
@@ -1241,6 +1214,65 @@ int exec_real(fft_plan p, const void* in, void* out, bool to_bins, float we, flo
     return ok();
 }
 
+// The sub-plan of a multidimensional plan (its last axis, or last two) over
+// `batch` of its transforms.
+int exec_last(fft_plan p, const void* in, void* out, int64_t batch, int sign, hipStream_t st)
+{
+    hipError_t e;
+    if (p->nd2_same) {
+        const KernelNd2* k = sign == p->sign ? p->nd2_same : p->nd2_opp;
+        e = k->fn(in, out, p->nd2_rows[0], p->nd2_rows[1], batch, p->scale, st);
+    } else if (p->fs) {
+        e = (sign < 0 ? p->fs->fwd : p->fs->bwd)(in, out, p->fs_rows1, p->fs_rows2, p->fs_tw,
+                                                 static_cast<const float2*>(p->fs_tw) + 1024, batch, p->scale, st);
+    } else {
+        const KernelC32* k = sign < 0 ? p->fwd : p->bwd;
+        e = (k->feed ? k->feed : k->fn)(in, out, p->tw, p->rows, batch, p->scale, p->grid_limit, st);
+    }
+    return e == hipSuccess ? ok() : hip_err(e, "last-axis kernel launch");
+}
+
+// A multidimensional plan of several passes: the last axis (or two) from in
+// to out, then the other axes in place in `out`.  Streams run chunk by chunk
+// (stream.hpp) of whole arrays; where a 3D array alone exceeds a chunk, its
+// first two passes take chunks of planes.  The first pass stores plainly, the
+// last one reads and writes a stream nontemporally.  MI355X at 2^26 points,
+// before -> after: 2048 x 2048 441 -> 378 us, 1024 x 1024 385 -> 331,
+// 512 x 512 366 -> 319, 128^3 442 -> 407, 256^3 587 -> 483,
+// 16 x 1024 x 1024 620 -> 491; 1024 x 1024 x 16 111 -> 87.
+int exec_nd(fft_plan p, const void* in, void* out, int sign, hipStream_t st)
+{
+    const bool stream = is_stream(p->total * (int64_t)sizeof(float2));
+    const float2* src = static_cast<const float2*>(in);
+    float2* dst = static_cast<float2*>(out);
+    // axis a over `points` points from offset `off` of out
+    auto axis = [&](int a, int64_t off, int64_t points) {
+        const KernelAxis* k = sign == p->sign ? p->ax_same[a] : p->ax_opp[a];
+        return k->fn(dst + off, p->ax_rows[a], points / p->dims[a], p->ax_log2s[a], p->ax_scale[a], stream && a == 0, st);
+    };
+    const int64_t n = p->n, unit = p->ax_first == 1 ? n / p->dims[0] : n;  // of the first two passes
+    const int64_t outer = stream ? chunk_units(n * (int64_t)sizeof(float2)) : p->batch;
+    for (int64_t b = 0; b < p->batch; b += outer) {
+        const int64_t off = b * n, points = std::min(outer, p->batch - b) * n;
+        const int64_t step = stream && p->ax_first == 1 ? chunk_units(unit * (int64_t)sizeof(float2)) * unit : points;
+        for (int64_t u = 0; u < points; u += step) {
+            const int64_t here = std::min(step, points - u);
+            int rc = exec_last(p->last, src + off + u, dst + off + u, here / p->last->n, sign, st);
+            if (rc != FFT_OK)
+                return rc;
+            if (p->ax_first == 1) {
+                const hipError_t e = axis(1, off + u, here);
+                if (e != hipSuccess)
+                    return hip_err(e, "axis kernel launch");
+            }
+        }
+        const hipError_t e = axis(0, off, points);
+        if (e != hipSuccess)
+            return hip_err(e, "axis kernel launch");
+    }
+    return ok();
+}
+
 // direction: the sign of the exponent actually applied; scale as given.
 int exec_c32(fft_plan p, const void* in, void* out, int sign, float scale, hipStream_t st)
 {
@@ -1258,19 +1290,8 @@ int exec_c32(fft_plan p, const void* in, void* out, int sign, float scale, hipSt
             return hip_err(e, "2D kernel launch");
         return ok();
     }
-    if (p->kind == 2) {
-        // last axis (batched 1D), then the other axes in place in `out`
-        int rc = exec_c32(p->last, in, out, sign, p->last->scale, st);
-        if (rc != FFT_OK)
-            return rc;
-        for (int a = p->ax_first; a >= 0; a--) {
-            const KernelAxis* k = sign == p->sign ? p->ax_same[a] : p->ax_opp[a];
-            hipError_t e = k->fn(out, p->ax_rows[a], p->ax_count[a], p->ax_log2s[a], p->ax_scale[a], st);
-            if (e != hipSuccess)
-                return hip_err(e, "axis kernel launch");
-        }
-        return ok();
-    }
+    if (p->kind == 2)
+        return exec_nd(p, in, out, sign, st);
     if (p->kind == 1) {
         int rc = ragged_execute(p->ragged, in, out, p->tw, sign, p->sign > 0, st);
         if (rc != FFT_OK)

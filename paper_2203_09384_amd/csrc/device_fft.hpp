@@ -596,13 +596,14 @@ __device__ __forceinline__ void load_group_part(cf (&v)[1 << E], const cf* __res
         v[m] = ld_data<NT>(gb + (off + (unsigned)(m * TPT * 8)));
 }
 
-template <int L, int E, int TPB>
+// PLAIN: plain stores whatever the shape.
+template <int L, int E, int TPB, bool PLAIN = false>
 __device__ __forceinline__ void store_group(const cf (&v)[1 << E], cf* __restrict__ out, int64_t g, int64_t batch,
                                             int tb, unsigned toff8, float scale)
 {
     using SC = Sched<L, E>;
     constexpr int N = SC::N, EPT = SC::EPT, TPT = SC::TPT;
-    constexpr bool NT = stream_nt<N, TPT>();
+    constexpr bool NT = stream_nt<N, TPT>() && !PLAIN;
     const int64_t first = g * TPB;
     char* gb = reinterpret_cast<char*>(out + first * N);
     // One transform per group: every group a kernel stores (g < batch) is

@@ -111,7 +111,8 @@ __global__ __launch_bounds__(WG) void k_fft_c32(const cf* __restrict__ in, cf* _
 // Global addresses are a uniform (SGPR) group base plus a 32-bit per-thread
 // byte offset; LDS addresses are one per-thread base plus immediates.
 
-template <int L, int E, int WG, int S, int TW, int PF, bool WAVE>
+// FEED: plain stores (the output is read again by another pass).
+template <int L, int E, int WG, int S, int TW, int PF, bool WAVE, bool FEED>
 __global__ __launch_bounds__(WG) void k_fft_c32_v2(const cf* __restrict__ in, cf* __restrict__ out,
                                                    const cf* __restrict__ rows, int64_t batch, float scale)
 {
@@ -141,7 +142,7 @@ __global__ __launch_bounds__(WG) void k_fft_c32_v2(const cf* __restrict__ in, cf
     if constexpr (!PF) {
         // one group per workgroup (the grid covers every group)
         run2<L, E, S, TW, WAVE>(a, t, rows, tws, my);
-        store_group<L, E, TPB>(a, out, g, batch, tb, toff8, scale);
+        store_group<L, E, TPB, FEED>(a, out, g, batch, tb, toff8, scale);
         return;
     }
     // Groups g, g + stride, ... ; `left` more after the current one.  The
@@ -161,33 +162,33 @@ __global__ __launch_bounds__(WG) void k_fft_c32_v2(const cf* __restrict__ in, cf
     int64_t left = (ngroups - 1 - g) / stride;
     if (left >= 2) {
         run2_prefetch<L, E, S, TW, WAVE, TPB>(a, t, rows, tws, my, b, in, g + stride, batch, tb, toff8);
-        store_group<L, E, TPB>(a, out, g, batch, tb, toff8, scale);
+        store_group<L, E, TPB, FEED>(a, out, g, batch, tb, toff8, scale);
         g += stride;
         lds_sync<WAVE>();  // LDS is reused by the next group
         while (true) {
             run2_prefetch<L, E, S, TW, WAVE, TPB>(b, t, rows, tws, my, a, in, g + stride, batch, tb, toff8);
-            store_group<L, E, TPB>(b, out, g, batch, tb, toff8, scale);
+            store_group<L, E, TPB, FEED>(b, out, g, batch, tb, toff8, scale);
             g += stride;
             lds_sync<WAVE>();
             left -= 2;
             if (left < 2)
                 break;
             run2_prefetch<L, E, S, TW, WAVE, TPB>(a, t, rows, tws, my, b, in, g + stride, batch, tb, toff8);
-            store_group<L, E, TPB>(a, out, g, batch, tb, toff8, scale);
+            store_group<L, E, TPB, FEED>(a, out, g, batch, tb, toff8, scale);
             g += stride;
             lds_sync<WAVE>();
         }
     }
     if (left == 1) {
         run2_prefetch<L, E, S, TW, WAVE, TPB>(a, t, rows, tws, my, b, in, g + stride, batch, tb, toff8);
-        store_group<L, E, TPB>(a, out, g, batch, tb, toff8, scale);
+        store_group<L, E, TPB, FEED>(a, out, g, batch, tb, toff8, scale);
         g += stride;
         lds_sync<WAVE>();
         run2<L, E, S, TW, WAVE>(b, t, rows, tws, my);
-        store_group<L, E, TPB>(b, out, g, batch, tb, toff8, scale);
+        store_group<L, E, TPB, FEED>(b, out, g, batch, tb, toff8, scale);
     } else {
         run2<L, E, S, TW, WAVE>(a, t, rows, tws, my);
-        store_group<L, E, TPB>(a, out, g, batch, tb, toff8, scale);
+        store_group<L, E, TPB, FEED>(a, out, g, batch, tb, toff8, scale);
     }
 }
 
@@ -200,7 +201,7 @@ __global__ __launch_bounds__(WG) void k_fft_c32_v2(const cf* __restrict__ in, cf
 // accesses hit distinct banks.  A thread reads its row, transforms it in
 // registers, writes its row back (no other thread touches it), and the
 // block leaves LDS the way it came in.
-template <int L, int WG, int S>
+template <int L, int WG, int S, bool FEED>
 __global__ __launch_bounds__(WG) void k_fft_c32_st(const cf* __restrict__ in, cf* __restrict__ out,
                                                    const cf* __restrict__ tw, int64_t batch, float scale)
 {
@@ -250,12 +251,12 @@ __global__ __launch_bounds__(WG) void k_fft_c32_st(const cf* __restrict__ in, cf
     if (count == WG) {
 #pragma unroll
         for (int k = 0; k < H; k++)
-            __builtin_nontemporal_store(q[k], dst + tid + WG * k);
+            st_data4<!FEED>(dst + tid + WG * k, q[k]);
     } else {
 #pragma unroll
         for (int k = 0; k < H; k++)
             if (tid + WG * k < nv)
-                __builtin_nontemporal_store(q[k], dst + tid + WG * k);
+                st_data4<!FEED>(dst + tid + WG * k, q[k]);
     }
 }
 
@@ -263,7 +264,7 @@ __global__ __launch_bounds__(WG) void k_fft_c32_st(const cf* __restrict__ in, cf
 // one wavefront): after the block is in LDS, thread t of a transform reads
 // its elements t + m TPT from the row, runs the passes with wavefront-local
 // exchanges in a separate region, and writes them back to the row.
-template <int L, int E, int WG, int S>
+template <int L, int E, int WG, int S, bool FEED>
 __global__ __launch_bounds__(WG) void k_fft_c32_st2(const cf* __restrict__ in, cf* __restrict__ out,
                                                     const cf* __restrict__ rows, int64_t batch, float scale)
 {
@@ -322,32 +323,32 @@ __global__ __launch_bounds__(WG) void k_fft_c32_st2(const cf* __restrict__ in, c
     if (count == TPB) {
 #pragma unroll
         for (int k = 0; k < K; k++)
-            __builtin_nontemporal_store(q[k], dst + tid + WG * k);
+            st_data4<!FEED>(dst + tid + WG * k, q[k]);
     } else {
 #pragma unroll
         for (int k = 0; k < K; k++)
             if (tid + WG * k < nv)
-                __builtin_nontemporal_store(q[k], dst + tid + WG * k);
+                st_data4<!FEED>(dst + tid + WG * k, q[k]);
     }
 }
 
-template <int L, int E, int WG, int S>
+template <int L, int E, int WG, int S, bool FEED = false>
 hipError_t launch_c32_st2(const void* in, void* out, const void*, const void* rows, int64_t batch, float scale,
                           int64_t, hipStream_t stream)
 {
     constexpr int TPB = WG / Sched<L, E>::TPT;
     const int64_t grid = (batch + TPB - 1) / TPB;
-    return launch_kernel((k_fft_c32_st2<L, E, WG, S>), dim3((unsigned)grid), dim3(WG), 0, stream,
+    return launch_kernel((k_fft_c32_st2<L, E, WG, S, FEED>), dim3((unsigned)grid), dim3(WG), 0, stream,
                        static_cast<const cf*>(in), static_cast<cf*>(out), static_cast<const cf*>(rows), batch,
                        scale);
 }
 
-template <int L, int WG, int S>
+template <int L, int WG, int S, bool FEED = false>
 hipError_t launch_c32_st(const void* in, void* out, const void* tw, const void*, int64_t batch, float scale,
                          int64_t, hipStream_t stream)
 {
     const int64_t grid = (batch + WG - 1) / WG;
-    return launch_kernel((k_fft_c32_st<L, WG, S>), dim3((unsigned)grid), dim3(WG), 0, stream,
+    return launch_kernel((k_fft_c32_st<L, WG, S, FEED>), dim3((unsigned)grid), dim3(WG), 0, stream,
                        static_cast<const cf*>(in), static_cast<cf*>(out), static_cast<const cf*>(tw), batch, scale);
 }
 
@@ -363,7 +364,7 @@ hipError_t launch_c32(const void* in, void* out, const void* tw, const void*, in
 }
 
 // grid_limit > 0 caps the number of (persistent) workgroups.
-template <int L, int E, int WG, int S, int TW, int PF, bool WAVE>
+template <int L, int E, int WG, int S, int TW, int PF, bool WAVE, bool FEED = false>
 hipError_t launch_c32_v2(const void* in, void* out, const void*, const void* rows, int64_t batch, float scale,
                          int64_t grid_limit, hipStream_t stream)
 {
@@ -371,7 +372,7 @@ hipError_t launch_c32_v2(const void* in, void* out, const void*, const void* row
     int64_t grid = (batch + TPB - 1) / TPB;
     if (grid_limit > 0 && grid > grid_limit)
         grid = grid_limit;
-    return launch_kernel((k_fft_c32_v2<L, E, WG, S, TW, PF, WAVE>), dim3((unsigned)grid), dim3(WG), 0, stream,
+    return launch_kernel((k_fft_c32_v2<L, E, WG, S, TW, PF, WAVE, FEED>), dim3((unsigned)grid), dim3(WG), 0, stream,
                        static_cast<const cf*>(in), static_cast<cf*>(out), static_cast<const cf*>(rows), batch,
                        scale);
 }
@@ -380,10 +381,17 @@ template <int L, int E, int WG, int S, int TW, int PF, bool WAVE>
 int occupancy_v2()
 {
     int blocks = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_fft_c32_v2<L, E, WG, S, TW, PF, WAVE>, WG, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_fft_c32_v2<L, E, WG, S, TW, PF, WAVE, false>, WG, 0) !=
         hipSuccess)
         return 0;
     return blocks;
+}
+
+// The built-in variant of its length: the one that multidimensional plans
+// run along the last axis, with plain stores.
+constexpr bool is_default(int L, int E, int WG, int kind)
+{
+    return kDefaultC32[L].log2ept == E && kDefaultC32[L].wg == WG && kDefaultC32[L].kind == kind;
 }
 
 // Variant menu, v1: EPT in {2,4,8,16} (not above N; at least 4 once
@@ -431,20 +439,23 @@ void add_one()
 {
     if constexpr (valid_cfg<LOG2N, LOG2EPT, WG>())
         register_c32(KernelC32{LOG2N, LOG2EPT, WG, S, 0, &launch_c32<LOG2N, LOG2EPT, WG, S>, nullptr, 0,
-                               ((1 << LOG2N) >> LOG2EPT) > 1 ? WG * (1 << LOG2EPT) * 8 : 0});
+                               ((1 << LOG2N) >> LOG2EPT) > 1 ? WG * (1 << LOG2EPT) * 8 : 0, nullptr});
 }
 
 template <int L, int E, int WG, int S, int TW, int PF>
 void add_v2()
 {
     if constexpr (valid_v2<L, E, WG>()) {
+        LaunchC32 feed = nullptr;
+        if constexpr (is_default(L, E, WG, 1 + TW + 2 * PF))
+            feed = &launch_c32_v2<L, E, WG, S, TW, PF, false, true>;
         register_c32(KernelC32{L, E, WG, S, 1 + TW + 2 * PF, &launch_c32_v2<L, E, WG, S, TW, PF, false>,
                                &occupancy_v2<L, E, WG, S, TW, PF, false>, Layout2<L, E>::rows_total(),
-                               (WG / ((1 << L) >> E)) * Layout2<L, E>::region() * 8});
+                               (WG / ((1 << L) >> E)) * Layout2<L, E>::region() * 8, feed});
         if constexpr (((1 << L) >> E) <= 64)
             register_c32(KernelC32{L, E, WG, S, 5 + TW + 2 * PF, &launch_c32_v2<L, E, WG, S, TW, PF, true>,
                                    &occupancy_v2<L, E, WG, S, TW, PF, true>, Layout2<L, E>::rows_total(),
-                                   (WG / ((1 << L) >> E)) * Layout2<L, E>::region() * 8});
+                                   (WG / ((1 << L) >> E)) * Layout2<L, E>::region() * 8, nullptr});
     }
 }
 
@@ -453,9 +464,13 @@ void add_v2()
 template <int LOG2N, int LOG2EPT, int WG, int S>
 void add_st()
 {
-    if constexpr (LOG2N >= 1 && LOG2N <= 4 && LOG2EPT == LOG2N && WG <= 256)
+    if constexpr (LOG2N >= 1 && LOG2N <= 4 && LOG2EPT == LOG2N && WG <= 256) {
+        LaunchC32 feed = nullptr;
+        if constexpr (is_default(LOG2N, LOG2EPT, WG, 11))
+            feed = &launch_c32_st<LOG2N, WG, S, true>;
         register_c32(KernelC32{LOG2N, LOG2EPT, WG, S, 11, &launch_c32_st<LOG2N, WG, S>, nullptr, 0,
-                               WG * ((1 << LOG2N) / 2 + ((1 << LOG2N) >= 4 ? 1 : 0)) * 16});
+                               WG * ((1 << LOG2N) / 2 + ((1 << LOG2N) >= 4 ? 1 : 0)) * 16, feed});
+    }
 }
 
 // kind 12: staged, several threads per transform (N = 32 .. 1024), 64..256 threads
@@ -464,10 +479,15 @@ void add_st2()
 {
     if constexpr (L >= 5 && L <= 10 && E >= 2 && E < L && WG <= 256) {
         constexpr int TPT = (1 << L) >> E;
-        if constexpr (TPT >= 2 && TPT <= 64 && TPT <= WG)
+        if constexpr (TPT >= 2 && TPT <= 64 && TPT <= WG) {
+            LaunchC32 feed = nullptr;
+            if constexpr (is_default(L, E, WG, 12))
+                feed = &launch_c32_st2<L, E, WG, S, true>;
             register_c32(KernelC32{L, E, WG, S, 12, &launch_c32_st2<L, E, WG, S>, nullptr,
                                    Layout2<L, E>::rows_total(),
-                                   (WG / TPT) * ((1 << L) / 2 + 1) * 16 + (WG / TPT) * Layout2<L, E>::region() * 8});
+                                   (WG / TPT) * ((1 << L) / 2 + 1) * 16 + (WG / TPT) * Layout2<L, E>::region() * 8,
+                                   feed});
+        }
     }
 }
 

@@ -18,34 +18,42 @@
 namespace mifft {
 namespace {
 
-template <int L, int S>
+template <int L, int S, bool NT>
 __global__ __launch_bounds__(axis_wg<L>()) void k_axis(cf* __restrict__ io, const cf* __restrict__ rows,
                                                         int64_t count, int log2s, float scale)
 {
     __shared__ cf lds[AXIS_TILE * stage_stride<L, axis_e(L)>()];
-    axis_tile_staged<L, S, false>(io, rows, lds, (int64_t)blockIdx.x * AXIS_TILE, count, log2s, scale);
+    axis_tile_staged<L, S, NT>(io, rows, lds, (int64_t)blockIdx.x * AXIS_TILE, count, log2s, scale);
 }
 
 // 512 points and more: 32 points per thread.
-template <int L, int S>
+template <int L, int S, bool NT>
 __global__ __launch_bounds__(Wide<L>::WG, WIDE_WAVES) void k_axis_wide(cf* __restrict__ io,
                                                                       const cf* __restrict__ rows, int64_t count,
                                                                       int log2s, float scale)
 {
     __shared__ float lds[Wide<L>::PLANE];
-    wide_axis_tile<L, S, false>(io, rows, lds, (int64_t)blockIdx.x * WIDE_TILE, count, log2s, scale);
+    wide_axis_tile<L, S, NT>(io, rows, lds, (int64_t)blockIdx.x * WIDE_TILE, count, log2s, scale);
 }
 
-template <int L, int S>
-hipError_t launch_axis(void* io, const void* rows, int64_t count, int log2s, float scale, hipStream_t stream)
+template <int L, int S, bool NT>
+hipError_t launch_axis_nt(cf* io, const cf* rows, int64_t count, int log2s, float scale, hipStream_t st)
 {
     const dim3 grid((unsigned)((count + AXIS_TILE - 1) / AXIS_TILE));
     if constexpr (wide_len(L))
-        return launch_kernel((k_axis_wide<L, S>), grid, dim3(Wide<L>::WG), 0, stream, static_cast<cf*>(io),
-                             static_cast<const cf*>(rows), count, log2s, scale);
+        return launch_kernel((k_axis_wide<L, S, NT>), grid, dim3(Wide<L>::WG), 0, st, io, rows, count, log2s, scale);
     else
-        return launch_kernel((k_axis<L, S>), grid, dim3(axis_wg<L>()), 0, stream, static_cast<cf*>(io),
-                             static_cast<const cf*>(rows), count, log2s, scale);
+        return launch_kernel((k_axis<L, S, NT>), grid, dim3(axis_wg<L>()), 0, st, io, rows, count, log2s, scale);
+}
+
+template <int L, int S>
+hipError_t launch_axis(void* io, const void* rows, int64_t count, int log2s, float scale, bool stream,
+                       hipStream_t st)
+{
+    cf* p = static_cast<cf*>(io);
+    const cf* r = static_cast<const cf*>(rows);
+    return stream ? launch_axis_nt<L, S, true>(p, r, count, log2s, scale, st)
+                  : launch_axis_nt<L, S, false>(p, r, count, log2s, scale, st);
 }
 
 template <int L>

@@ -11,8 +11,9 @@ namespace mifft {
 // stride 2^log2s elements; transform q starts at element
 // (q >> log2s) * 2^(log2n + log2s) + (q & (2^log2s - 1)).  rows: the
 // transform's per-pass twiddle rows; every output is multiplied by scale.
+// stream: nontemporal loads and stores.
 using LaunchAxis = hipError_t (*)(void* io, const void* rows, int64_t count, int log2s, float scale,
-                                  hipStream_t stream);
+                                  bool stream, hipStream_t st);
 
 struct KernelAxis {
     int log2n;

@@ -15,6 +15,32 @@ namespace mifft {
 using LaunchC32 = hipError_t (*)(const void* in, void* out, const void* tw, const void* rows, int64_t batch,
                                  float scale, int64_t grid_limit, hipStream_t stream);
 
+struct Variant {
+    int log2ept, wg, kind;
+};
+
+// Built-in choice per log2 N (index 1..11) for FP32: the autotuner's pick on
+// MI355X at 2^26 elements per launch (log2 EPT, workgroup size, variant).
+constexpr Variant kDefaultC32[21] = {
+    {0, 0, 0},     // unused
+    {1, 64, 11},   // N=2     one thread per transform, block staged through LDS
+    {2, 128, 11},  // N=4
+    {3, 64, 11},   // N=8
+    {4, 128, 11},  // N=16
+    {3, 64, 12},   // N=32    several threads per transform, block staged through LDS
+    {3, 256, 12},  // N=64
+    {3, 64, 12},   // N=128
+    {4, 128, 12},  // N=256
+    {3, 64, 12},   // N=512
+    {4, 64, 3},    // N=1024  persistent, next-group prefetch
+    {4, 128, 3},   // N=2048  persistent, next-group prefetch
+    {3, 512, 3},   // N=2^12  one transform per workgroup
+    {4, 512, 3},   // N=2^13
+    {4, 1024, 2},  // N=2^14  135 KiB LDS
+    {0, 0, 9},     // N=2^15 .. 2^20: four-step (column + row pass)
+    {0, 0, 9}, {0, 0, 9}, {0, 0, 9}, {0, 0, 9}, {0, 0, 9},
+};
+
 struct KernelC32 {
     int log2n, log2ept, wg, sign;
     int kind;                 // 0: one transform group per workgroup, per-pass table reads
@@ -24,6 +50,10 @@ struct KernelC32 {
     int (*occupancy)();       // workgroups per CU (persistent kinds), else NULL
     int rows;                 // twiddle-row entries the variant needs (kind >= 1)
     int lds_bytes;            // LDS per workgroup
+    // the same with plain stores, which stay in the memory-side cache for the
+    // next pass of a multidimensional transform; compiled for the built-in
+    // variant of each length, else NULL
+    LaunchC32 feed;
 };
 
 void register_c32(const KernelC32& k);

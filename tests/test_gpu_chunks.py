@@ -31,3 +31,18 @@ def test_four_step_chunks(L, sign):
     at = torch.tensor([0, per - 1, per, batch - 1], device="cuda")
     xs = to_cpu(x[at]).astype(np.complex128)
     assert per_transform_relerr(to_cpu(y[at]), oracle.forward(xs) if sign < 0 else oracle.inverse(xs)) <= TOL
+
+
+@pytest.mark.parametrize("shape,batch", [((512, 1024), 67), ((64, 128, 128), 33), ((64, 512, 1024), 1),
+                                         ((256, 512, 512), 1), ((4, 32768), 258)], ids=str)
+@pytest.mark.parametrize("sign", [-1, 1])
+def test_nd_chunks(shape, batch, sign):
+    """Chunks of whole arrays, and of planes where one array exceeds a chunk
+    (256 x 512 x 512: 512 MiB)."""
+    n = int(np.prod(shape))
+    x = signal(batch, *shape)
+    print(f"[case] nd chunks shape={shape} batch={batch} sign={sign}", flush=True)
+    y = api.PlanND(shape, batch, sign).execute(x)
+    for b in {0, batch - 1}:
+        ref = oracle.fftn(to_cpu(x[b:b + 1]).astype(np.complex128), len(shape), sign, 1.0 if sign < 0 else 1.0 / n)
+        assert per_transform_relerr(to_cpu(y[b]).reshape(1, -1), ref.reshape(1, -1)) <= TOL
