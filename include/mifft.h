@@ -132,14 +132,14 @@ typedef struct {
  *          LDS); 2^15 .. 2^20 (the paper's future work, section
  *          "Conclusions") use the four-step split N = N1 N2: a column pass
  *          with the w_N^{n2 k1} twiddles, then an in-place row pass in
- *          `out` (two kernels on the stream).  FFT_C16 / FFT_CBF16: [2, 2048]
+ *          `out` (two kernels on the stream per 256 MiB of input).  FFT_C16 / FFT_CBF16: [2, 2048]
  *          (2048: radix-16 passes on MFMA; below: the FP32 passes with
  *          16-bit storage).
  *          FFT_R32: [2, 2^21]; up to 2^15 one fused kernel per
- *          execute, above it the half-length four-step transform plus a
- *          split pass through a plan-owned workspace of n/2 complex values
- *          per transform (allocated here; executes of one such plan must
- *          not overlap in time).
+ *          execute, above it the half-length four-step transform with the
+ *          split folded into its passes, through a plan-owned workspace of
+ *          n/2 complex values per transform, at most 128 MiB (allocated
+ *          here; executes of one such plan must not overlap in time).
  *   batch  >= 1.
  *   sign   -1: forward transform Eq. (dft), scale 1.
  *          +1: inverse transform Eq. (idft), scale 1/n.
@@ -246,8 +246,8 @@ int fft_execute(fft_plan p, const void *in, void *out, void *stream);
  * while they execute (code under stream capture, tight serving loops,
  * harnesses that forbid allocation): fft_execute with every intermediate in
  * memory the library already holds.  Allocates nothing and frees nothing.
- *   FFT_R32 plans above 2^15 (the half-length four-step transform plus the
- *   split pass): the intermediate spectrum of n/2 complex values per
+ *   FFT_R32 plans above 2^15 (the half-length four-step transform with the
+ *   split): the intermediate spectrum of n/2 complex values per
  *   transform goes to a static scratch array of MIFFT_STATIC_SCRATCH_BYTES
  *   per GPU instead of the plan's workspace, so (n/2) * batch * 8 bytes must
  *   fit: FFT_EINVAL_BATCH otherwise, with the largest batch for that length

@@ -338,6 +338,7 @@ struct mifft_plan_s {
     mifft_plan_s* real_sub = nullptr;
     void* real_ws = nullptr;
     void* real_tw = nullptr;
+    void* real_rows[2] = {nullptr, nullptr};  // inner transforms, 32 points per thread
     // multidimensional plans (kind 2): the last axis as a batched sub-plan,
     // then in-place axis passes from the second-to-last axis to the first
     int rank = 1;
@@ -663,7 +664,7 @@ void free_plan(mifft_plan_s* p)
         free_plan(p->last);
     if (p->real_sub)
         free_plan(p->real_sub);
-    for (void* q : {p->real_ws, p->real_tw})
+    for (void* q : {p->real_ws, p->real_tw, p->real_rows[0], p->real_rows[1]})
         if (q)
             (void)hipFree(q);
     for (void* q : {p->ax_rows[0], p->ax_rows[1], p->nd2_rows[0], p->nd2_rows[1], p->nd3_rows})
@@ -717,13 +718,22 @@ fft_plan create_real_large(int64_t n, int64_t batch, int sign)
     p->total = n * batch;
     p->real_sub = sub;
     p->var = Variant{0, 0, 9};
-    hipError_t e = hipMalloc(&p->real_ws, (size_t)m * (size_t)batch * sizeof(float2));
-    if (e != hipSuccess) {
+    const FourStep* f = sub->fs;
+    const int Ls[2] = {f->log2n1, f->log2n2};
+    int counts[2];
+    hipError_t e = hipMalloc(&p->real_ws, (size_t)m * (size_t)fs_ws_transforms(m, batch) * sizeof(float2));
+    if (e != hipSuccess)
         p->real_ws = nullptr;
-    } else {
+    if (e == hipSuccess) {
         e = hipMalloc(&p->real_tw, (size_t)(1024 + n / 1024) * sizeof(float2));
         if (e != hipSuccess)
             p->real_tw = nullptr;
+    }
+    for (int i = 0; i < 2 && e == hipSuccess; i++) {
+        counts[i] = idx::rows_total(Ls[i], 5);
+        e = hipMalloc(&p->real_rows[i], (size_t)counts[i] * sizeof(float2));
+        if (e != hipSuccess)
+            p->real_rows[i] = nullptr;
     }
     if (e != hipSuccess) {
         e == hipErrorOutOfMemory ? set_err(FFT_ENOMEM, "hipMalloc(real-input workspace) failed")
@@ -732,6 +742,8 @@ fft_plan create_real_large(int64_t n, int64_t batch, int sign)
         return nullptr;
     }
     e = launch_twiddle_big(p->real_tw, static_cast<float2*>(p->real_tw) + 1024, p->log2n, nullptr);
+    for (int i = 0; i < 2 && e == hipSuccess; i++)
+        e = launch_twiddle_rows(sub->tw, p->real_rows[i], Ls[i], 5, counts[i], nullptr);
     if (e == hipSuccess)
         e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) {
@@ -1180,8 +1192,6 @@ int check_exec(fft_plan p, const void* in, const void* out, bool to_bins = false
     return FFT_OK;
 }
 
-int exec_c32(fft_plan p, const void* in, void* out, int sign, float scale, hipStream_t st);
-
 // FFT_R32: to_bins selects the real -> bins kernel; we / wi weight the
 // edge and interior bins (see real.hip).  ws: the workspace of a plan above
 // 2^15 (n/2 complex values per transform), NULL for the plan's own.
@@ -1189,23 +1199,12 @@ int exec_real(fft_plan p, const void* in, void* out, bool to_bins, float we, flo
               void* ws = nullptr)
 {
     if (p->real_sub) {
-        // Z = DFT_{n/2}(z) into the workspace, then the split (or the
-        // reverse); the complex transform runs unscaled, the weights carry
-        // the plan's scale
-        const float2* tw = static_cast<const float2*>(p->real_tw);
-        if (!ws)
-            ws = p->real_ws;
-        if (to_bins) {
-            int rc = exec_c32(p->real_sub, in, ws, -1, 1.0f, st);
-            if (rc != FFT_OK)
-                return rc;
-            hipError_t e = launch_real_split(0, ws, out, tw, tw + 1024, p->log2n, p->batch, we, wi, st);
-            return e == hipSuccess ? ok() : hip_err(e, "real-input split launch");
-        }
-        hipError_t e = launch_real_split(1, in, ws, tw, tw + 1024, p->log2n, p->batch, we, wi, st);
-        if (e != hipSuccess)
-            return hip_err(e, "real-input split launch");
-        return exec_c32(p->real_sub, ws, out, +1, 1.0f, st);
+        const mifft_plan_s* sub = p->real_sub;
+        const float2 *tw = static_cast<const float2*>(p->real_tw), *fs = static_cast<const float2*>(sub->fs_tw);
+        const RealTables t{sub->fs_rows1, sub->fs_rows2, fs, fs + 1024, p->real_rows[0], p->real_rows[1], tw, tw + 1024};
+        const hipError_t e = to_bins ? sub->fs->r2c(in, out, ws ? ws : p->real_ws, t, p->batch, we, wi, st)
+                                     : sub->fs->c2r(in, out, t, p->batch, we, wi, st);
+        return e == hipSuccess ? ok() : hip_err(e, "real-input FFT kernel launch");
     }
     const KernelReal* k = to_bins ? p->r2c : p->c2r;
     hipError_t e = k->fn(in, out, p->rows, p->wn, p->batch, we, wi, p->grid_limit, st);

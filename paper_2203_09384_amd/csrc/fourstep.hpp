@@ -10,6 +10,21 @@ using LaunchFourStep = hipError_t (*)(const void* in, void* out, const void* row
                                       const void* tlo, const void* thi, int64_t batch, float scale,
                                       hipStream_t stream);
 
+// Tables of a real-input plan above 2^15 (half length M = N1 N2, n = 2 M):
+// the four-step plan's rows and two-level w_M; rows of 32 points per thread
+// of both inner transforms; two-level w_n.
+struct RealTables {
+    const void *rows1, *rows2, *tlo, *thi;
+    const void *wide1, *wide2, *rlo, *rhi;
+};
+
+// we / wi weight the edge bins (0 and M) and the interior ones.  R2C's ws
+// holds fs_ws_transforms(M, batch) M complex values.
+using LaunchFsR2C = hipError_t (*)(const void* in, void* out, void* ws, const RealTables& t, int64_t batch, float we,
+                                   float wi, hipStream_t stream);
+using LaunchFsC2R = hipError_t (*)(const void* in, void* out, const RealTables& t, int64_t batch, float we, float wi,
+                                   hipStream_t stream);
+
 struct FourStep {
     int log2n, log2n1, log2n2;  // N = N1 * N2, column length N1, row length N2
     int log2e1, log2e2;         // elements per thread of the inner transforms
@@ -17,10 +32,13 @@ struct FourStep {
     LaunchFourStep fwd, bwd;    // sign -1 / +1
     int lds1, lds2;             // LDS per workgroup of each pass
     int tile1;                  // columns per pass-1 workgroup
+    LaunchFsR2C r2c;            // real input of twice the length (M >= 2^15)
+    LaunchFsC2R c2r;
 };
 
 void register_fourstep(const FourStep& f);
 const FourStep* find_fourstep(int log2n);
+int64_t fs_ws_transforms(int64_t m, int64_t batch);
 hipError_t launch_twiddle_big(void* lo, void* hi, int L, hipStream_t stream);
 
 }  // namespace mifft

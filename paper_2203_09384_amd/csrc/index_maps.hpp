@@ -188,6 +188,21 @@ MIFFT_HD constexpr int64_t xcd_group_tile(int64_t b, int G)
     return (b & ~int64_t(8 * G - 1)) + G * (b & 7) + ((b >> 3) & (G - 1));
 }
 
+// Tile `tile` of transform b for block `block`, PER tiles per transform: of
+// every 8 whole transforms each XCD takes one, tile after tile; the
+// transforms left over are dealt in order.
+struct Tile {
+    int64_t b, tile;
+};
+MIFFT_HD constexpr Tile xcd_deal_tile(int64_t block, int64_t batch, int64_t per)
+{
+    const int64_t whole = (batch & ~int64_t(7)) * per;
+    if (block >= whole)
+        return Tile{block / per, block % per};
+    const int64_t group = block / (8 * per), i = block % (8 * per);
+    return Tile{8 * group + (i & 7), i >> 3};
+}
+
 // Element n of transform q of an axis of length 2^L and stride 2^log2s:
 // transforms adjacent in memory are consecutive q, the array of
 // 2^(L + log2s) elements repeats.

@@ -27,23 +27,35 @@ __global__ __launch_bounds__(axis_wg<L>()) void k_axis(cf* __restrict__ io, cons
 }
 
 // 512 points and more: 32 points per thread.
-template <int L, int S, bool NT>
-__global__ __launch_bounds__(Wide<L>::WG, WIDE_WAVES) void k_axis_wide(cf* __restrict__ io,
+template <int L, int S, bool NT, int T>
+__global__ __launch_bounds__((Wide<L, T>::WG), WIDE_WAVES) void k_axis_wide(cf* __restrict__ io,
                                                                       const cf* __restrict__ rows, int64_t count,
                                                                       int log2s, float scale)
 {
-    __shared__ float lds[Wide<L>::PLANE];
-    wide_axis_tile<L, S, NT>(io, rows, lds, (int64_t)blockIdx.x * WIDE_TILE, count, log2s, scale);
+    __shared__ float lds[Wide<L, T>::PLANE];
+    const int64_t q0 = idx::xcd_group_tile(blockIdx.x, WIDE_TILE / T) * T;
+    if (q0 < count)
+        wide_axis_tile<L, S, NT, T>(io, rows, lds, q0, count, log2s, scale);
+}
+
+template <int L, int S, bool NT, int T>
+hipError_t launch_axis_wide(cf* io, const cf* rows, int64_t count, int log2s, float scale, hipStream_t st)
+{
+    const int64_t tiles = (count + T - 1) / T, chunk = 8 * (WIDE_TILE / T);
+    const dim3 grid((unsigned)(T == WIDE_TILE ? tiles : (tiles + chunk - 1) / chunk * chunk));
+    return launch_kernel((k_axis_wide<L, S, NT, T>), grid, dim3(Wide<L, T>::WG), 0, st, io, rows, count, log2s,
+                         scale);
 }
 
 template <int L, int S, bool NT>
 hipError_t launch_axis_nt(cf* io, const cf* rows, int64_t count, int log2s, float scale, hipStream_t st)
 {
     const dim3 grid((unsigned)((count + AXIS_TILE - 1) / AXIS_TILE));
-    if constexpr (wide_len(L))
-        return launch_kernel((k_axis_wide<L, S, NT>), grid, dim3(Wide<L>::WG), 0, st, io, rows, count, log2s, scale);
-    else
+    if constexpr (!wide_len(L)) {
         return launch_kernel((k_axis<L, S, NT>), grid, dim3(axis_wg<L>()), 0, st, io, rows, count, log2s, scale);
+    } else {
+        return launch_axis_wide<L, S, NT, 16>(io, rows, count, log2s, scale, st);
+    }
 }
 
 template <int L, int S>

@@ -17,8 +17,8 @@
 // 370 -> 366.
 //
 // Thread (t, c), c the tile's transform and the fastest lane index, holds
-// points t + m TPT.  Plane element d of transform c is at pad(d) 16 + c:
-// the 16 transforms are interleaved, so a wavefront's access covers 16
+// points t + m TPT.  Plane element d of transform c is at pad(d) T + c:
+// the T = 16 transforms are interleaved, so a wavefront's access covers 16
 // transforms x 4 points and is conflict-free when the 4 padded indices
 // differ mod 4.
 #pragma once
@@ -30,15 +30,16 @@ namespace mifft {
 constexpr int WIDE_E = 5, WIDE_TILE = 16;
 constexpr bool wide_len(int L) { return L >= 9 && L <= 11; }
 // pad(d) = d + (d >> B): one spare row of the plane every 2^B points, which
-// makes the writes of the first 512- and 1024-point pass and every read
+// makes the writes of the first pass (up to 1024 points) and every read
 // conflict-free (the radix-2 pass of 2048 points writes two-way).
-constexpr int wide_pad(int L) { return L == 9 ? 4 : 5; }
+constexpr int wide_pad(int L) { return L <= 10 ? L - 5 : 5; }
 
-template <int L>
+// T transforms (16, or 32 for the two row groups of the real split).
+template <int L, int T = WIDE_TILE>
 struct Wide {
     using SC = Sched<L, WIDE_E>;
-    static constexpr int N = 1 << L, EPT = 32, TPT = N / EPT, WG = TPT * WIDE_TILE;
-    static constexpr int PLANE = (N + (N >> wide_pad(L))) * WIDE_TILE;  // floats
+    static constexpr int N = 1 << L, EPT = 32, TPT = N / EPT, WG = TPT * T;
+    static constexpr int PLANE = (N + (N >> wide_pad(L))) * T;  // floats
 };
 
 // Wavefronts per SIMD that the registers are limited for (128 per lane): one
@@ -66,12 +67,12 @@ constexpr bool wide_pad_splits(int L, int P)
 }
 
 // One plane of the exchange after pass P: COMP 0 real parts, 1 imaginary.
-template <int L, int P, int COMP>
+template <int L, int P, int COMP, int T>
 __device__ __forceinline__ void wide_plane(cf (&v)[32], int t, float* lds)
 {
     using SC = typename Wide<L>::SC;
     constexpr int LR = SC::log2r(P), R = 1 << LR, LNS = SC::log2ns(P), NS = 1 << LNS;
-    constexpr int TPT = Wide<L>::TPT, Q = 32 / R, B = wide_pad(L), T = WIDE_TILE;
+    constexpr int TPT = Wide<L>::TPT, Q = 32 / R, B = wide_pad(L);
     static_assert(wide_pad_splits(L, P), "padded addresses are a thread base plus immediates");
     const int k = t & (NS - 1), d0 = ((t >> LNS) << (LNS + LR)) + k;
     float* w = lds + (d0 + (d0 >> B)) * T;
@@ -130,7 +131,7 @@ __device__ __forceinline__ void wide_twiddle(cf (&v)[32], cf (&w)[4], const cf* 
 // All passes of the tile's transforms; v in and out as points t + m TPT.
 // `lds` is the tile's plane offset by the transform index c; `w` the first
 // four twiddles of pass P.
-template <int L, int S, int P = 0>
+template <int L, int S, int T = WIDE_TILE, int P = 0>
 __device__ __forceinline__ void wide_run(cf (&v)[32], int t, const cf* __restrict__ rows, float* lds, cf (&w)[4])
 {
     using SC = typename Wide<L>::SC;
@@ -145,23 +146,23 @@ __device__ __forceinline__ void wide_run(cf (&v)[32], int t, const cf* __restric
             __syncthreads();  // the previous exchange is read
         cf nx[4];
         wide_row_part<L, S, P + 1, 0>(nx, rows, t);
-        wide_plane<L, P, 0>(v, t, lds);
+        wide_plane<L, P, 0, T>(v, t, lds);
         __syncthreads();
-        wide_plane<L, P, 1>(v, t, lds);
-        wide_run<L, S, P + 1>(v, t, rows, lds, nx);
+        wide_plane<L, P, 1, T>(v, t, lds);
+        wide_run<L, S, T, P + 1>(v, t, rows, lds, nx);
     }
 }
 
-// Axis pass over transforms q0 .. q0 + 15 below `count`, in place: a thread
+// Axis pass over transforms q0 .. q0 + T - 1 below `count`, in place: a thread
 // loads and stores its points straight from and to HBM, at the same
 // addresses, nontemporally if NT.  Transforms past the end read transform q0
 // and store nothing.
-template <int L, int S, bool NT>
+template <int L, int S, bool NT, int T>
 __device__ __forceinline__ void wide_axis_tile(cf* __restrict__ io, const cf* __restrict__ rows, float* lds,
                                                int64_t q0, int64_t count, int log2s, float scale)
 {
-    constexpr int TPT = Wide<L>::TPT;
-    const int tid = threadIdx.x, c = tid & (WIDE_TILE - 1), t = tid / WIDE_TILE;
+    constexpr int TPT = Wide<L, T>::TPT;
+    const int tid = threadIdx.x, c = tid & (T - 1), t = tid / T;
     const int64_t q = q0 + c;
     const bool live = q < count;
     char* p = reinterpret_cast<char*>(io + idx::axis_elem(live ? q : q0, t, L, log2s));
@@ -171,7 +172,7 @@ __device__ __forceinline__ void wide_axis_tile(cf* __restrict__ io, const cf* __
     for (int m = 0; m < 32; m++)
         v[m] = ld_data<NT>(p + m * step);
     cf w[4];
-    wide_run<L, S>(v, t, rows, lds + c, w);
+    wide_run<L, S, T>(v, t, rows, lds + c, w);
     // The stores' addresses are computed again: kept from the loads, the 32
     // of them would take 64 registers through the passes.
     asm volatile("" : "+s"(step));
