@@ -438,10 +438,14 @@ __global__ __launch_bounds__((Wide<L1, T>::WG), WIDE_WAVES) void k_unsplit_cols(
     col_store<L1, T>(v, lds, ws + (b * PER + nb) * (T * N1), tid);
 }
 
-// fn(integral_constant<int, T>) with the tile width T.
+// fn(integral_constant<int, T>) with the tile width T for `count` transforms
+// (streams have enough tiles of 16).
 template <bool NT, class F>
-hipError_t with_tile(int64_t, F fn)
+hipError_t with_tile(int64_t count, F fn)
 {
+    if constexpr (!NT)
+        if (narrow_tiles(count))
+            return fn(std::integral_constant<int, 8>{});
     return fn(std::integral_constant<int, 16>{});
 }
 

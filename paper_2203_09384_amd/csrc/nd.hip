@@ -54,6 +54,9 @@ hipError_t launch_axis_nt(cf* io, const cf* rows, int64_t count, int log2s, floa
     if constexpr (!wide_len(L)) {
         return launch_kernel((k_axis<L, S, NT>), grid, dim3(axis_wg<L>()), 0, st, io, rows, count, log2s, scale);
     } else {
+        if constexpr (!NT)
+            if (narrow_tiles(count))
+                return launch_axis_wide<L, S, false, 8>(io, rows, count, log2s, scale, st);
         return launch_axis_wide<L, S, NT, 16>(io, rows, count, log2s, scale, st);
     }
 }

@@ -183,4 +183,16 @@ __device__ __forceinline__ void wide_axis_tile(cf* __restrict__ io, const cf* __
     }
 }
 
+// Tiles of 8 transforms where tiles of 16 would be fewer than two per CU:
+// 256 CUs with one or two workgroups each finish unevenly, and a single
+// transform or image does not reach all of them.  Tiles that share 128-byte
+// lines run on one XCD (xcd_group_tile).  MI355X, tiles of 16 -> 8, us:
+//   2^20 x 1 23.3 -> 19.4, x 5 39.6 -> 36.0, x 8 (512 tiles) 50.6 -> 54.1
+//   2D 2048 x 2048 x 1 39.9 -> 36.6, x 3 85.8 -> 74.5; 1024 x 1024 x 1
+//   17.5 -> 16.0, x 8 (512 tiles) 47.1 -> 48.5
+//   real 2^20 x 1: R2C 24.4 -> 19.9, C2R 22.3 -> 18.0
+// (Tiles of 4 gained at most 0.5 us more, at one or two transforms, and
+// lost 2-10 us from 4 transforms on.)
+inline bool narrow_tiles(int64_t count) { return count < 2 * 256 * WIDE_TILE; }
+
 }  // namespace mifft
