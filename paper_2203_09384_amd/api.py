@@ -1,6 +1,11 @@
 """Python binding of the mifft C ABI: plans, execute calls and the
 differentiable FFT.  Argument marshalling only -- every transform runs in
 the HIP kernels of libmifft.so; torch provides device memory and streams.
+
+The ordinary case of each call (plain dense GPU tensors of the plan's type
+and size, the current stream) is made in C++ (csrc/torch_calls.cpp), which
+returns NotImplemented for anything else; the code here then handles or
+refuses it.
 """
 from __future__ import annotations
 
@@ -10,7 +15,7 @@ import threading
 import torch
 
 from . import native
-from .native import FFT_C16, FFT_C32, FFT_CBF16, FFT_R32, MifftError, check, check_plan, lib
+from .native import FFT_C16, FFT_C32, FFT_CBF16, FFT_R32, MifftError, calls, check, check_plan, lib
 
 DTYPES = {"c32": FFT_C32, "c16": FFT_C16, "cbf16": FFT_CBF16, "r32": FFT_R32}
 _HALF_TORCH = {FFT_C16: torch.float16, FFT_CBF16: torch.bfloat16}
@@ -63,7 +68,11 @@ class Plan:
                                          int(ept or 0), int(wg or 0), int(variant))
         else:
             h = L.fft_plan_create(self.n, self.batch, self.sign, self.dtype)
-        self._h = check_plan(h)
+        self._own(check_plan(h))
+
+    def _own(self, h):
+        self._h = h
+        self._ref = calls().plan(h, self.dtype, self.sign, self.n, self.batch)
 
     # -- marshalling -------------------------------------------------------
     def _check_tensor(self, x, what, side=None):
@@ -115,15 +124,27 @@ class Plan:
 
     def execute(self, x, out=None, stream=None):
         """out = plan(x); allocates `out` (torch caching allocator) if not given."""
+        if stream is None:
+            y = calls().run(self._ref, x, out, False)
+            if y is not NotImplemented:
+                return y
         return self._run(lib().fft_execute, x, out, stream, self.sign < 0)
 
     def adjoint(self, g, out=None, stream=None):
         """out = plan^H(g): conjugate sign, same scale (real-input plans: the
         adjoint under Re<a, b>, from the spectrum side for sign -1)."""
+        if stream is None:
+            y = calls().run(self._ref, g, out, True)
+            if y is not NotImplemented:
+                return y
         return self._run(lib().fft_execute_adjoint, g, out, stream, self.sign > 0)
 
     def execute_scaled(self, x, in_exp=None, out=None, out_exp=None, stream=None):
         """Block floating point (FP16/BF16 plans): value = stored * 2^exp[b]."""
+        if in_exp is None and out is None and out_exp is None and stream is None:
+            r = calls().scaled(self._ref, x)
+            if r is not NotImplemented:
+                return r
         self._check_tensor(x, "input")
         if out is None:
             out = torch.empty_like(x)
@@ -169,14 +190,13 @@ class Plan:
 
     def close(self):
         if getattr(self, "_h", None):
-            lib().fft_plan_destroy(self._h)
+            calls().close(self._ref)
             self._h = None
 
     def __del__(self):
-        try:
-            self.close()
-        except Exception:
-            pass
+        # graphs that still need the plan share it (close() takes it from
+        # them too)
+        self._ref = None
 
 
 class _DeviceArray:
@@ -211,6 +231,7 @@ class RaggedPlan:
         else:
             h = L.fft_plan_create_ragged(self.count, op, self.sign, self.dtype)
         self._h = check_plan(h)
+        self._ref = calls().plan(self._h, self.dtype, self.sign, self.total, 1)
 
     def _check_tensor(self, x, what):
         if not x.is_cuda or not x.is_contiguous() or x.dtype != torch.complex64:
@@ -219,6 +240,10 @@ class RaggedPlan:
             raise ValueError(f"{what} has {x.numel()} elements, plan needs {self.total}")
 
     def execute(self, x, out=None, stream=None):
+        if stream is None:
+            y = calls().run(self._ref, x, out, False)
+            if y is not NotImplemented:
+                return y
         self._check_tensor(x, "input")
         if out is None:
             out = torch.empty_like(x)
@@ -227,6 +252,10 @@ class RaggedPlan:
         return out
 
     def adjoint(self, g, out=None, stream=None):
+        if stream is None:
+            y = calls().run(self._ref, g, out, True)
+            if y is not NotImplemented:
+                return y
         self._check_tensor(g, "input")
         if out is None:
             out = torch.empty_like(g)
@@ -241,14 +270,13 @@ class RaggedPlan:
 
     def close(self):
         if getattr(self, "_h", None):
-            lib().fft_plan_destroy(self._h)
+            calls().close(self._ref)
             self._h = None
 
     def __del__(self):
-        try:
-            self.close()
-        except Exception:
-            pass
+        # graphs that still need the plan share it (close() takes it from
+        # them too)
+        self._ref = None
 
 
 # ------------------------------------------------------------------ plan cache
@@ -280,6 +308,9 @@ def get_plan(n: int, batch: int, sign: int, dtype: str = "c32", device=None) -> 
 
 def fft(x, sign: int = -1):
     """Transform over the last dimension of a complex64 GPU tensor (new tensor)."""
+    y = calls().call(_cache, x, sign, "c32", 0, 0, False)
+    if y is not NotImplemented:
+        return y
     x = x.contiguous()
     n = x.shape[-1]
     return get_plan(n, x.numel() // n, sign, "c32", x.device.index).execute(x)
@@ -313,6 +344,9 @@ class FFTFn(torch.autograd.Function):
 
 
 def fft_differentiable(x, sign: int = -1):
+    y = calls().call(_cache, x, sign, "c32", 0, 0, True)
+    if y is not NotImplemented:
+        return y
     return FFTFn.apply(x, sign)
 
 
@@ -346,6 +380,9 @@ class WeightedPowerLossFn(torch.autograd.Function):
 
 
 def weighted_power_loss(x, w, sign: int = -1):
+    y = calls().loss(_cache, x, w, sign)
+    if y is not NotImplemented:
+        return y
     return WeightedPowerLossFn.apply(x, w, sign)
 
 
@@ -353,6 +390,9 @@ def weighted_power_loss(x, w, sign: int = -1):
 def rfft(x):
     """Bins 0..n/2 of the forward transform of a real float32 GPU tensor
     (last dimension n) as a new complex64 tensor (..., n/2 + 1)."""
+    y = calls().call(_cache, x, -1, "r32", 0, 0, False)
+    if y is not NotImplemented:
+        return y
     x = x.contiguous()
     n = x.shape[-1]
     return get_plan(n, x.numel() // n, -1, "r32", x.device.index).execute(x)
@@ -361,8 +401,11 @@ def rfft(x):
 def irfft(X, n: int | None = None):
     """Inverse of rfft: n reals (default 2 * (bins - 1)) from n/2 + 1 bins,
     with the 1/n of Eq. (idft); imaginary parts of bins 0 and n/2 ignored."""
-    X = X.contiguous()
     n = 2 * (X.shape[-1] - 1) if n is None else int(n)
+    x = calls().call(_cache, X, +1, "r32", 0, n, False)
+    if x is not NotImplemented:
+        return x
+    X = X.contiguous()
     if X.shape[-1] != n // 2 + 1:
         raise ValueError(f"{X.shape[-1]} bins given, n={n} needs {n // 2 + 1}")
     return get_plan(n, X.numel() // (n // 2 + 1), +1, "r32", X.device.index).execute(X)
@@ -406,11 +449,17 @@ class IRFFTFn(torch.autograd.Function):
 
 
 def rfft_differentiable(x):
+    y = calls().call(_cache, x, -1, "r32", 0, 0, True)
+    if y is not NotImplemented:
+        return y
     return RFFTFn.apply(x)
 
 
 def irfft_differentiable(X, n: int | None = None):
     n = 2 * (X.shape[-1] - 1) if n is None else int(n)
+    x = calls().call(_cache, X, +1, "r32", 0, n, True)
+    if x is not NotImplemented:
+        return x
     return IRFFTFn.apply(X, n)
 
 
@@ -426,7 +475,7 @@ class PlanND(Plan):
         self.n = int(np.prod(self.dims))
         self.batch, self.sign, self.dtype = int(batch), int(sign), FFT_C32
         arr = (ctypes.c_int64 * len(self.dims))(*self.dims)
-        self._h = check_plan(L.fft_plan_create_nd(len(self.dims), arr, self.batch, self.sign, FFT_C32))
+        self._own(check_plan(L.fft_plan_create_nd(len(self.dims), arr, self.batch, self.sign, FFT_C32)))
 
 
 def _nd_plan(shape, batch, sign, device):
@@ -445,8 +494,11 @@ def _nd_plan(shape, batch, sign, device):
 def fftn(x, ndim: int | None = None, sign: int = -1):
     """Transform over the last `ndim` dimensions (default all, at most 3) of
     a complex64 GPU tensor; new tensor."""
-    x = x.contiguous()
     ndim = x.dim() if ndim is None else int(ndim)
+    y = calls().call(_cache, x, sign, "nd", ndim, 0, False)
+    if y is not NotImplemented:
+        return y
+    x = x.contiguous()
     shape = tuple(x.shape[x.dim() - ndim:])
     n = 1
     for d in shape:
@@ -488,4 +540,7 @@ class FFTNFn(torch.autograd.Function):
 
 
 def fftn_differentiable(x, ndim: int, sign: int = -1):
+    y = calls().call(_cache, x, sign, "nd", ndim, 0, True)
+    if y is not NotImplemented:
+        return y
     return FFTNFn.apply(x, ndim, sign)

@@ -1,4 +1,5 @@
-"""Build libmifft.so (HIP, gfx950) in-tree with hipcc.
+"""Build libmifft.so (HIP, gfx950) in-tree with hipcc, and the Python
+binding's C++ calls (_mifft_torch.so) beside it.
 
 Every kernel translation unit is compiled for gfx950 only; the FP32 Stockham
 file is compiled once per transform length (-DMIFFT_LOG2N=1..14), the
@@ -11,6 +12,7 @@ import concurrent.futures as cf
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -18,6 +20,9 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmifft.so")
 # measurement support for the benchmark: a plain streaming copy (HBM ceiling)
 COPY_LIB = os.path.join(HERE, "libstreamcopy.so")
+# the Python binding's calls on torch tensors (host C++ against torch's headers)
+CALLS_LIB = os.path.join(HERE, "_mifft_torch.so")
+CXX = os.environ.get("CXX", "g++")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # Packed FP32 instructions are disabled for every device compile.
@@ -56,16 +61,33 @@ def _compile(src, obj, extra):
     return r.stderr
 
 
+def _build_calls():
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = CALLS_LIB + ".tmp"
+    cmd = [CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I" + os.path.join(root, "include"), "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-I/opt/rocm/include", "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "torch_calls.cpp"),
+           "-o", tmp, "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"build of the torch calls failed:\n{r.stderr}")
+    os.replace(tmp, CALLS_LIB)
+
+
 def build(jobs: int | None = None, verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     units = _units()
     jobs = jobs or min(16, max(1, len(os.sched_getaffinity(0))))
     with cf.ThreadPoolExecutor(jobs) as ex:
+        calls = ex.submit(_build_calls)
         futs = [ex.submit(_compile, *u) for u in units]
         for f in futs:
             msg = f.result()
             if verbose and msg.strip():
                 print(msg, file=sys.stderr)
+        calls.result()
     objs = [os.path.join(BUILD, u[1]) for u in units]
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs

@@ -8,10 +8,13 @@ already loaded (one runtime per process).
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libmifft.so")
+CALLS_PATH = os.path.join(HERE, "_mifft_torch.so")
 
 FFT_C32, FFT_C16, FFT_CBF16, FFT_R32 = 0, 1, 2, 3
 STATUS = {
@@ -111,6 +114,28 @@ def _declare(L):
     L.fft_version.argtypes = []
     L.fft_version.restype = ctypes.c_char_p
     return L
+
+
+_calls = None
+
+
+def calls():
+    """The C++ calls on torch tensors (csrc/torch_calls.cpp), bound to the
+    loaded library's entry points."""
+    global _calls
+    if _calls is None:
+        L = lib()
+        if not os.path.exists(CALLS_PATH):
+            raise ImportError(f"{CALLS_PATH} is not built; run __graft_entry__.build() "
+                              "(or python -m paper_2203_09384_amd.build)")
+        loader = importlib.machinery.ExtensionFileLoader("_mifft_torch", CALLS_PATH)
+        m = importlib.util.module_from_spec(importlib.util.spec_from_loader("_mifft_torch", loader))
+        loader.exec_module(m)
+        m.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in
+                 (L.fft_execute, L.fft_execute_adjoint, L.fft_execute_loss_grad, L.fft_execute_scaled,
+                  L.fft_plan_destroy)), check)
+        _calls = m
+    return _calls
 
 
 def check(rc: int):
