@@ -106,12 +106,13 @@ static std::vector<FourStep>& fs_reg()
     return r;
 }
 void register_fourstep(const FourStep& f) { fs_reg().push_back(f); }
-const FourStep* find_fourstep(int log2n)
+const FourStep* find_fourstep(int log2n, int64_t bytes)
 {
+    const FourStep* found = nullptr;
     for (const auto& f : fs_reg())
-        if (f.log2n == log2n)
-            return &f;
-    return nullptr;
+        if (f.log2n == log2n && (!f.bulk || is_bulk(bytes)) && (!found || f.bulk))
+            found = &f;
+    return found;
 }
 static std::vector<KernelLossGrad>& lg_reg()
 {
@@ -145,12 +146,13 @@ static std::vector<KernelAxis>& axis_reg()
     return r;
 }
 void register_axis(const KernelAxis& k) { axis_reg().push_back(k); }
-const KernelAxis* find_axis(int log2n, int sign)
+const KernelAxis* find_axis(int log2n, int sign, int64_t bytes)
 {
+    const KernelAxis* found = nullptr;
     for (const auto& k : axis_reg())
-        if (k.log2n == log2n && k.sign == sign)
-            return &k;
-    return nullptr;
+        if (k.log2n == log2n && k.sign == sign && (!k.bulk || is_bulk(bytes)) && (!found || k.bulk))
+            found = &k;
+    return found;
 }
 static std::vector<KernelNd2>& nd2_reg()
 {
@@ -389,7 +391,7 @@ int check_common(int64_t n, int64_t batch, int sign, int dtype)
 int fill_desc_fourstep(int64_t n, int64_t batch, int sign, int dtype, fft_plan_desc* d)
 {
     memset(d, 0, sizeof *d);
-    const FourStep* f = find_fourstep(ilog2(n));
+    const FourStep* f = find_fourstep(ilog2(n), n * batch * (int64_t)sizeof(float2));
     d->n = n;
     d->batch = batch;
     d->sign = sign;
@@ -528,7 +530,7 @@ int make_twiddles(mifft_plan_s* p)
 // w_N table.
 int make_fourstep(mifft_plan_s* p)
 {
-    const FourStep* f = find_fourstep(p->log2n);
+    const FourStep* f = find_fourstep(p->log2n, p->total * (int64_t)sizeof(float2));
     p->fs = f;
     const size_t nt = 1024 + ((size_t)1 << (p->log2n - 10));
     hipError_t e = hipMalloc(&p->fs_rows1, std::max(f->rows1, 1) * sizeof(float2));
@@ -817,7 +819,7 @@ fft_plan create_batched(int64_t n, int64_t batch, int sign, int dtype, const Var
     const bool four_step = dtype == FFT_C32 && n > 2048 &&
                            (force ? force->kind == 9 : choose_c32(log2n).kind == 9);
     if (four_step) {
-        const FourStep* f = find_fourstep(log2n);
+        const FourStep* f = find_fourstep(log2n, n * batch * (int64_t)sizeof(float2));
         if (!f) {
             set_err(FFT_EINVAL_N, "no four-step kernels for n=%lld", (long long)n);
             return nullptr;
@@ -1073,7 +1075,7 @@ fft_plan create_nd(int rank, const int64_t* dims, int64_t batch, int sign, int d
     if (rank == 1)
         return create_batched(dims[0], batch, sign, dtype, nullptr);
     for (int a = 0; a + 1 < rank; a++) {
-        const KernelAxis* k = find_axis(ilog2(dims[a]), sign);
+        const KernelAxis* k = find_axis(ilog2(dims[a]), sign, n * batch * (int64_t)sizeof(float2));
         if (!k) {
             set_err(FFT_EINVAL_CONFIG, "no axis kernel compiled for length %lld", (long long)dims[a]);
             return nullptr;
@@ -1125,8 +1127,8 @@ fft_plan create_nd(int rank, const int64_t* dims, int64_t batch, int sign, int d
     p->ax_first = tail2 ? 0 : rank - 2;
     for (int a = p->ax_first; a >= 0; a--) {
         const int L = ilog2(dims[a]);
-        p->ax_same[a] = find_axis(L, sign);
-        p->ax_opp[a] = find_axis(L, -sign);
+        p->ax_same[a] = find_axis(L, sign, p->total * (int64_t)sizeof(float2));
+        p->ax_opp[a] = find_axis(L, -sign, p->total * (int64_t)sizeof(float2));
         p->ax_log2s[a] = log2s;
         p->ax_scale[a] = sign > 0 ? 1.0f / (float)dims[a] : 1.0f;
         log2s += L;
@@ -1690,7 +1692,7 @@ int fft_plan_query(int64_t n, int64_t batch, int sign, int dtype, fft_plan_desc*
     if (rc != FFT_OK)
         return rc;
     if (dtype == FFT_R32 && n > kMaxFusedRealN) {
-        if (!find_fourstep(ilog2(n) - 1))
+        if (!find_fourstep(ilog2(n) - 1, 0))
             return set_err(FFT_EINVAL_CONFIG, "no four-step kernels for the half length of n=%lld", (long long)n);
         fill_desc_r32(n, batch, sign, Variant{0, 0, 9}, 0, d);
         return ok();
@@ -1715,7 +1717,7 @@ int fft_plan_query(int64_t n, int64_t batch, int sign, int dtype, fft_plan_desc*
         return ok();
     }
     const Variant v = choose_c32(ilog2(n));
-    if (v.kind == 9 ? !find_fourstep(ilog2(n)) : !find_c32(ilog2(n), v.log2ept, v.wg, sign, v.kind))
+    if (v.kind == 9 ? !find_fourstep(ilog2(n), 0) : !find_c32(ilog2(n), v.log2ept, v.wg, sign, v.kind))
         return set_err(FFT_EINVAL_CONFIG, "no FP32 kernel compiled for n=%lld", (long long)n);
     fill_desc_c32(n, batch, sign, dtype, v, 0, d);
     return ok();

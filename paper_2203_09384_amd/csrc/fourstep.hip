@@ -450,11 +450,11 @@ hipError_t with_tile(int64_t count, F fn)
 }
 
 // Pass 2 in place: the axis pass of stride N1 over batch N1 transforms.
-template <int L1, int L2, int S, bool NT>
+template <int L1, int L2, int S, bool NT, bool W>
 hipError_t launch_rows(cf* io, const void* rows2, int64_t batch, float scale, hipStream_t stream)
 {
     const cf* rows = static_cast<const cf*>(rows2);
-    if constexpr (wide_len(L2))
+    if constexpr (wide_len(L2, W))
         return with_tile<NT>(batch << L1, [&](auto tc) {
             constexpr int T = decltype(tc)::value;
             return launch_kernel((k_fourstep2_wide<L1, L2, S, NT, T>), dim3((unsigned)(batch * ((1 << L1) / T))),
@@ -466,11 +466,11 @@ hipError_t launch_rows(cf* io, const void* rows2, int64_t batch, float scale, hi
 }
 
 // Pass 1.
-template <int L1, int L2, int S, bool NT>
+template <int L1, int L2, int S, bool NT, bool W>
 hipError_t launch_cols(const cf* in, cf* out, const cf* rows1, const cf* tlo, const cf* thi, int64_t batch,
                        hipStream_t stream)
 {
-    if constexpr (wide_len(L1))
+    if constexpr (wide_len(L1, W))
         return with_tile<NT>(batch << L2, [&](auto tc) {
             constexpr int T = decltype(tc)::value;
             return launch_kernel((k_fourstep1_wide<L1, L2, S, NT, T>), dim3((unsigned)(batch * ((1 << L2) / T))),
@@ -483,12 +483,12 @@ hipError_t launch_cols(const cf* in, cf* out, const cf* rows1, const cf* tlo, co
 
 // Both passes over `batch` transforms.  NT: the column pass reads and the
 // row pass reads and writes nontemporally; the column pass stores plainly.
-template <int L1, int L2, int S, bool NT>
+template <int L1, int L2, int S, bool NT, bool W>
 hipError_t launch_passes(const cf* in, cf* out, const cf* rows1, const cf* rows2, const cf* tlo, const cf* thi,
                          int64_t batch, float scale, hipStream_t stream)
 {
-    const hipError_t e = launch_cols<L1, L2, S, NT>(in, out, rows1, tlo, thi, batch, stream);
-    return e == hipSuccess ? launch_rows<L1, L2, S, NT>(out, rows2, batch, scale, stream) : e;
+    const hipError_t e = launch_cols<L1, L2, S, NT, W>(in, out, rows1, tlo, thi, batch, stream);
+    return e == hipSuccess ? launch_rows<L1, L2, S, NT, W>(out, rows2, batch, scale, stream) : e;
 }
 
 // Streams run chunk by chunk (stream.hpp): the row pass reads what the
@@ -496,7 +496,7 @@ hipError_t launch_passes(const cf* in, cf* out, const cf* rows1, const cf* rows2
 // and plain accesses -> this: 2^15 427 -> 351 us, 2^16 437 -> 350, 2^17
 // 438 -> 349, 2^18 444 -> 348, 2^19 448 -> 366, 2^20 446 -> 377; at 256 MiB 2^16
 // 221 -> 176 (nontemporal accesses alone).
-template <int L1, int L2, int S>
+template <int L1, int L2, int S, bool W>
 hipError_t launch_fourstep(const void* in, void* out, const void* rows1, const void* rows2, const void* tlo,
                            const void* thi, int64_t batch, float scale, hipStream_t stream)
 {
@@ -505,11 +505,11 @@ hipError_t launch_fourstep(const void* in, void* out, const void* rows1, const v
     cf* dst = static_cast<cf*>(out);
     constexpr int64_t EACH = int64_t(sizeof(cf)) << (L1 + L2);
     if (!is_stream(batch * EACH))
-        return launch_passes<L1, L2, S, false>(src, dst, r1, r2, lo, hi, batch, scale, stream);
+        return launch_passes<L1, L2, S, false, W>(src, dst, r1, r2, lo, hi, batch, scale, stream);
     const int64_t per = chunk_units(EACH);
     for (int64_t b = 0; b < batch; b += per) {
         const int64_t nb = batch - b < per ? batch - b : per;
-        const hipError_t e = launch_passes<L1, L2, S, true>(src + (b << (L1 + L2)), dst + (b << (L1 + L2)), r1, r2,
+        const hipError_t e = launch_passes<L1, L2, S, true, W>(src + (b << (L1 + L2)), dst + (b << (L1 + L2)), r1, r2,
                                                             lo, hi, nb, scale, stream);
         if (e != hipSuccess)
             return e;
@@ -526,20 +526,20 @@ constexpr int64_t real_chunk(int64_t m) { return chunk_units(2 * m * (int64_t)si
 // Real input, M = 2^(L1 + L2): R2C through `ws`, which holds one chunk (the
 // whole batch unless it is a stream) and is used again by every chunk; C2R
 // needs no workspace (column pass into `out`, row pass in place).
-template <int L1, int L2>
+template <int L1, int L2, bool W>
 hipError_t launch_r2c(const void* in, void* out, void* ws, const RealTables& t, int64_t batch, float we, float wi,
                       hipStream_t stream)
 {
     constexpr int64_t M = int64_t(1) << (L1 + L2);
-    const cf *rows1 = static_cast<const cf*>(wide_len(L1) ? t.wide1 : t.rows1), *lo = static_cast<const cf*>(t.tlo),
+    const cf *rows1 = static_cast<const cf*>(wide_len(L1, W) ? t.wide1 : t.rows1), *lo = static_cast<const cf*>(t.tlo),
              *hi = static_cast<const cf*>(t.thi);
     const bool big = is_stream(batch * M * (int64_t)sizeof(cf));
     const int64_t per = big ? real_chunk(M) : batch;
     for (int64_t b = 0; b < batch; b += per) {
         const int64_t nb = batch - b < per ? batch - b : per;
         const cf* src = static_cast<const cf*>(in) + b * M;
-        hipError_t e = big ? launch_cols<L1, L2, -1, true>(src, static_cast<cf*>(ws), rows1, lo, hi, nb, stream)
-                           : launch_cols<L1, L2, -1, false>(src, static_cast<cf*>(ws), rows1, lo, hi, nb, stream);
+        hipError_t e = big ? launch_cols<L1, L2, -1, true, W>(src, static_cast<cf*>(ws), rows1, lo, hi, nb, stream)
+                           : launch_cols<L1, L2, -1, false, W>(src, static_cast<cf*>(ws), rows1, lo, hi, nb, stream);
         if (e == hipSuccess)
             e = with_tile<false>(nb << (L1 - 1), [&](auto tc) {
                 constexpr int T = 2 * decltype(tc)::value;
@@ -554,7 +554,7 @@ hipError_t launch_r2c(const void* in, void* out, void* ws, const RealTables& t, 
     return hipSuccess;
 }
 
-template <int L1, int L2>
+template <int L1, int L2, bool W>
 hipError_t launch_c2r(const void* in, void* out, const RealTables& t, int64_t batch, float we, float wi,
                       hipStream_t stream)
 {
@@ -573,8 +573,8 @@ hipError_t launch_c2r(const void* in, void* out, const RealTables& t, int64_t ba
                                  static_cast<const cf*>(t.rhi), nb, we, wi);
         });
         if (e == hipSuccess)
-            e = big ? launch_rows<L1, L2, +1, true>(dst, t.rows2, nb, 1.f, stream)
-                    : launch_rows<L1, L2, +1, false>(dst, t.rows2, nb, 1.f, stream);
+            e = big ? launch_rows<L1, L2, +1, true, W>(dst, t.rows2, nb, 1.f, stream)
+                    : launch_rows<L1, L2, +1, false, W>(dst, t.rows2, nb, 1.f, stream);
         if (e != hipSuccess)
             return e;
     }
@@ -582,12 +582,12 @@ hipError_t launch_c2r(const void* in, void* out, const RealTables& t, int64_t ba
 }
 
 // log2 of the points per thread, and the LDS bytes, of an inner transform.
-constexpr int fs_e(int Li) { return wide_len(Li) ? WIDE_E : inner_e(Li); }
+constexpr int fs_e(int Li, bool W) { return wide_len(Li, W) ? WIDE_E : inner_e(Li); }
 
-template <int Li>
+template <int Li, bool W>
 constexpr int fs_lds()
 {
-    if constexpr (wide_len(Li))
+    if constexpr (wide_len(Li, W))
         return Wide<Li>::PLANE * (int)sizeof(float);
     else
         return TILE * stage_stride<Li, inner_e(Li)>() * (int)sizeof(cf);
@@ -599,24 +599,24 @@ struct RealFns {
 };
 
 // Half lengths of the real-input plans above 2^15.
-template <int L1, int L2>
+template <int L1, int L2, bool W>
 constexpr RealFns real_fns()
 {
     if constexpr (L1 + L2 >= 15)
-        return RealFns{&launch_r2c<L1, L2>, &launch_c2r<L1, L2>};
+        return RealFns{&launch_r2c<L1, L2, W>, &launch_c2r<L1, L2, W>};
     else
         return RealFns{nullptr, nullptr};
 }
 
-template <int L>
+template <int L, bool W = false>
 void add_len()
 {
     constexpr int L1 = (L + 1) / 2, L2 = L / 2;
-    constexpr int E1 = fs_e(L1), E2 = fs_e(L2);
+    constexpr int E1 = fs_e(L1, W), E2 = fs_e(L2, W);
     const int tw = tw3_in_lds(L) ? (64 + (1 << (L - 10))) * (int)sizeof(cf) : 0;
     const FourStep fs{L, L1, L2, E1, E2, Layout2<L1, E1>::rows_total(), Layout2<L2, E2>::rows_total(),
-                      &launch_fourstep<L1, L2, -1>, &launch_fourstep<L1, L2, +1>, fs_lds<L1>() + tw, fs_lds<L2>(),
-                      TILE, real_fns<L1, L2>().r2c, real_fns<L1, L2>().c2r};
+                      &launch_fourstep<L1, L2, -1, W>, &launch_fourstep<L1, L2, +1, W>, fs_lds<L1, W>() + tw,
+                      fs_lds<L2, W>(), TILE, real_fns<L1, L2, W>().r2c, real_fns<L1, L2, W>().c2r, W};
     register_fourstep(fs);
 }
 
@@ -627,8 +627,11 @@ struct FourStepRegistrar {
         add_len<13>();
         add_len<14>();
         add_len<15>();
+        add_len<15, true>();
         add_len<16>();
+        add_len<16, true>();
         add_len<17>();
+        add_len<17, true>();
         add_len<18>();
         add_len<19>();
         add_len<20>();

@@ -34,10 +34,12 @@ struct FourStep {
     int tile1;                  // columns per pass-1 workgroup
     LaunchFsR2C r2c;            // real input of twice the length (M >= 2^15)
     LaunchFsC2R c2r;
+    bool bulk;                  // for calls that fill the chip (is_bulk)
 };
 
 void register_fourstep(const FourStep& f);
-const FourStep* find_fourstep(int log2n);
+// The kernels for calls of `bytes` per direction.
+const FourStep* find_fourstep(int log2n, int64_t bytes);
 int64_t fs_ws_transforms(int64_t m, int64_t batch);
 hipError_t launch_twiddle_big(void* lo, void* hi, int L, hipStream_t stream);
 

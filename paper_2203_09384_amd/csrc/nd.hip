@@ -26,7 +26,7 @@ __global__ __launch_bounds__(axis_wg<L>()) void k_axis(cf* __restrict__ io, cons
     axis_tile_staged<L, S, NT>(io, rows, lds, (int64_t)blockIdx.x * AXIS_TILE, count, log2s, scale);
 }
 
-// 512 points and more: 32 points per thread.
+// 512 points and more (128 and 256 in large calls): 32 points per thread.
 template <int L, int S, bool NT, int T>
 __global__ __launch_bounds__((Wide<L, T>::WG), WIDE_WAVES) void k_axis_wide(cf* __restrict__ io,
                                                                       const cf* __restrict__ rows, int64_t count,
@@ -47,11 +47,11 @@ hipError_t launch_axis_wide(cf* io, const cf* rows, int64_t count, int log2s, fl
                          scale);
 }
 
-template <int L, int S, bool NT>
+template <int L, int S, bool NT, bool W>
 hipError_t launch_axis_nt(cf* io, const cf* rows, int64_t count, int log2s, float scale, hipStream_t st)
 {
     const dim3 grid((unsigned)((count + AXIS_TILE - 1) / AXIS_TILE));
-    if constexpr (!wide_len(L)) {
+    if constexpr (!wide_len(L, W)) {
         return launch_kernel((k_axis<L, S, NT>), grid, dim3(axis_wg<L>()), 0, st, io, rows, count, log2s, scale);
     } else {
         if constexpr (!NT)
@@ -61,28 +61,28 @@ hipError_t launch_axis_nt(cf* io, const cf* rows, int64_t count, int log2s, floa
     }
 }
 
-template <int L, int S>
+template <int L, int S, bool W>
 hipError_t launch_axis(void* io, const void* rows, int64_t count, int log2s, float scale, bool stream,
                        hipStream_t st)
 {
     cf* p = static_cast<cf*>(io);
     const cf* r = static_cast<const cf*>(rows);
-    return stream ? launch_axis_nt<L, S, true>(p, r, count, log2s, scale, st)
-                  : launch_axis_nt<L, S, false>(p, r, count, log2s, scale, st);
+    return stream ? launch_axis_nt<L, S, true, W>(p, r, count, log2s, scale, st)
+                  : launch_axis_nt<L, S, false, W>(p, r, count, log2s, scale, st);
 }
 
-template <int L>
+template <int L, bool W = false>
 void add_axis()
 {
-    constexpr int E = wide_len(L) ? WIDE_E : axis_e(L);
+    constexpr int E = wide_len(L, W) ? WIDE_E : axis_e(L);
     const int rows = ((1 << L) >> E) > 1 ? Layout2<L, E>::rows_total() : 0;
     int lds;
-    if constexpr (wide_len(L))
+    if constexpr (wide_len(L, W))
         lds = Wide<L>::PLANE * (int)sizeof(float);
     else
         lds = AXIS_TILE * stage_stride<L, E>() * (int)sizeof(cf);
-    register_axis(KernelAxis{L, E, -1, AXIS_TILE, &launch_axis<L, -1>, rows, lds});
-    register_axis(KernelAxis{L, E, +1, AXIS_TILE, &launch_axis<L, +1>, rows, lds});
+    register_axis(KernelAxis{L, E, -1, AXIS_TILE, &launch_axis<L, -1, W>, rows, lds, W});
+    register_axis(KernelAxis{L, E, +1, AXIS_TILE, &launch_axis<L, +1, W>, rows, lds, W});
 }
 
 struct AxisRegistrar {
@@ -95,7 +95,9 @@ struct AxisRegistrar {
         add_axis<5>();
         add_axis<6>();
         add_axis<7>();
+        add_axis<7, true>();
         add_axis<8>();
+        add_axis<8, true>();
         add_axis<9>();
         add_axis<10>();
         add_axis<11>();

@@ -23,9 +23,11 @@ struct KernelAxis {
     LaunchAxis fn;
     int rows;       // twiddle-row entries (float2)
     int lds_bytes;
+    bool bulk;  // for calls that fill the chip (is_bulk)
 };
 
 void register_axis(const KernelAxis& k);
-const KernelAxis* find_axis(int log2n, int sign);
+// The kernel for calls of `bytes` per direction.
+const KernelAxis* find_axis(int log2n, int sign, int64_t bytes);
 
 }  // namespace mifft

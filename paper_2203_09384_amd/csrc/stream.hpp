@@ -24,6 +24,15 @@ namespace mifft {
 constexpr int64_t kStreamBytes = int64_t(128) << 20;
 constexpr int64_t kChunkBytes = int64_t(256) << 20;
 
+// Passes of 128 and 256 points keep 32 points per thread (wide_tile.hpp) in
+// calls that fill the chip several times over, for the loads in flight; in
+// smaller ones 8 or 16 points per thread make four or two times the
+// wavefronts.  MI355X, 8 / 16 -> 32 points per thread, us: four-step 2^16 at
+// 64 MiB 51.0 -> 43.0, at 512 MiB 349 -> 346, at 16 MiB 22.6 -> 23.3, at 2 MiB
+// 10.9 -> 12.0; 2D 256 x 256 at 64 MiB 49.2 -> 44.3.
+constexpr int64_t kBulkBytes = int64_t(32) << 20;
+inline bool is_bulk(int64_t bytes) { return bytes > kBulkBytes; }
+
 // Whether a call that reads `bytes` and writes about as much is a stream.
 inline bool is_stream(int64_t bytes) { return bytes > kStreamBytes; }
 

@@ -1,5 +1,5 @@
-// Tiles of 16 adjacent transforms of 512, 1024 or 2048 points, 32 points
-// per thread: the long axis passes and the long passes of the four-step.
+// Tiles of 16 adjacent transforms of 512, 1024 or 2048 points (in large
+// calls 128 and 256 too), 32 points per thread: the long axis passes and the long passes of the four-step.
 //
 // These passes are bound by memory bandwidth, and reach it only in whole
 // 128-byte lines: on MI355X a copy of 2048-point columns at 2^26 points
@@ -28,7 +28,8 @@
 namespace mifft {
 
 constexpr int WIDE_E = 5, WIDE_TILE = 16;
-constexpr bool wide_len(int L) { return L >= 9 && L <= 11; }
+// W: 128 and 256 points too (is_bulk in stream.hpp says when).
+constexpr bool wide_len(int L, bool W) { return (L >= 9 && L <= 11) || (W && (L == 7 || L == 8)); }
 // pad(d) = d + (d >> B): one spare row of the plane every 2^B points, which
 // makes the writes of the first pass (up to 1024 points) and every read
 // conflict-free (the radix-2 pass of 2048 points writes two-way).
