@@ -201,9 +201,29 @@ const Variant kDefaultR32[15] = {
     {4, 256, 3},   // n=1024
     {4, 64, 3},    // n=2048
     {4, 128, 3},   // n=4096
-    {4, 256, 3},   // n=2^13  one transform per workgroup
-    {4, 512, 3},   // n=2^14
+    {3, 512, 3},   // n=2^13  one transform per workgroup
+    {4, 512, 2},   // n=2^14
     {4, 1024, 2},  // n=2^15
+};
+
+// Smaller calls (see kRulesC32 in registry.hpp for why).  MI355X, R2C + C2R
+// together in us, default -> rule, by MiB of reals:
+//   n=32    16: 18.7 -> 16.8, 32: 29.6 -> 27.5 (48: 53.6 -> 57.9)
+//   n=64    16: 18.2 -> 15.9, 32: 31.1 -> 24.6 (64: 65.3 -> 63.7, 512: 439 -> 476)
+//   n=256   32: 29.5 -> 27.0, 64: 51.6 -> 48.1, 96: 84.2 -> 79.2 (128: 109 -> 109)
+//   n=512   0.5: 9.6 -> 6.6, 8: 12.1 -> 9.8, 16: 18.3 -> 16.6 (48: 41.9 -> 41.1)
+//   n=1024  0.5: 11.6 -> 6.8, 8: 13.5 -> 9.7, 32: 32.0 -> 28.0; 64: 56.0 -> 48.4,
+//           128: 109 -> 102 (512: 409 -> 416)
+//   n=2048  0.5: 8.0 -> 7.2, 16: 21.9 -> 18.0; 32: 35.3 -> 29.5, 64: 57.6 -> 51.3
+//           (128: 104 -> 104)
+//   n=2^12  0.5: 9.5 -> 7.7, 16: 22.5 -> 18.5, 32: 35.7 -> 31.3 (64: 55.8 -> 58.6)
+//   n=2^13  0.5: 13.4 -> 10.3, 16: 22.4 -> 19.9, 32: 36.4 -> 33.4 (64: 59.9 -> 62.1)
+// The defaults themselves at 512 MiB: n=2^13 with 16 points per thread 441,
+// with 8 411; n=2^14 persistent 652 us, one transform per workgroup 510.
+constexpr SizeRule kRulesR32[] = {
+    {4, 32, {2, 128, 7}},   {5, 32, {2, 256, 7}},  {7, 24, {3, 256, 6}},   {7, 96, {2, 256, 7}},
+    {8, 24, {3, 128, 6}},   {9, 32, {3, 64, 6}},   {9, 192, {3, 256, 7}},  {10, 24, {3, 128, 2}},
+    {10, 96, {3, 256, 3}},  {11, 32, {3, 256, 2}}, {12, 32, {3, 512, 2}},
 };
 
 // Fused loss-gradient kernel (two transforms per group, so its own best
@@ -269,7 +289,8 @@ void load_tune_table()
     }
 }
 
-Variant choose_c32(int log2n)
+// bytes: of the call, per direction.
+Variant choose_c32(int log2n, int64_t bytes)
 {
     std::call_once(g_tune_once, load_tune_table);
     if (g_have_tuned_c32[log2n]) {
@@ -277,7 +298,7 @@ Variant choose_c32(int log2n)
         if ((v.kind == 9 && log2n > 11) || find_c32(log2n, v.log2ept, v.wg, -1, v.kind))
             return v;
     }
-    return kDefaultC32[log2n];
+    return rule_or(kRulesC32, log2n, bytes, kDefaultC32[log2n]);
 }
 
 Variant choose_loss(int log2n)
@@ -286,7 +307,7 @@ Variant choose_loss(int log2n)
     return g_have_tuned_loss[log2n] ? g_tuned_loss[log2n] : kDefaultLoss[log2n];
 }
 
-Variant choose_r32(int log2m)
+Variant choose_r32(int log2m, int64_t bytes)
 {
     std::call_once(g_tune_once, load_tune_table);
     if (g_have_tuned_r32[log2m]) {
@@ -294,7 +315,7 @@ Variant choose_r32(int log2m)
         if (find_real(log2m, v.log2ept, v.wg, 0, v.kind) && find_real(log2m, v.log2ept, v.wg, 1, v.kind))
             return v;
     }
-    return kDefaultR32[log2m];
+    return rule_or(kRulesR32, log2m, bytes, kDefaultR32[log2m]);
 }
 
 // Stockham schedule of (log2 N, log2 EPT): a remainder pass first, then
@@ -767,7 +788,7 @@ fft_plan create_real(int64_t n, int64_t batch, int sign, const Variant* force)
         return create_real_large(n, batch, sign);
     }
     const int log2m = ilog2(n) - 1;
-    const Variant v = force ? *force : choose_r32(log2m);
+    const Variant v = force ? *force : choose_r32(log2m, n * batch * 4);
     const KernelReal* r2c = find_real(log2m, v.log2ept, v.wg, 0, v.kind);
     const KernelReal* c2r = find_real(log2m, v.log2ept, v.wg, 1, v.kind);
     if (!r2c || !c2r) {
@@ -817,7 +838,7 @@ fft_plan create_batched(int64_t n, int64_t batch, int sign, int dtype, const Var
     const int log2n = ilog2(n);
     Variant v{};
     const bool four_step = dtype == FFT_C32 && n > 2048 &&
-                           (force ? force->kind == 9 : choose_c32(log2n).kind == 9);
+                           (force ? force->kind == 9 : choose_c32(log2n, n * batch * 8).kind == 9);
     if (four_step) {
         const FourStep* f = find_fourstep(log2n, n * batch * (int64_t)sizeof(float2));
         if (!f) {
@@ -838,7 +859,7 @@ fft_plan create_batched(int64_t n, int64_t batch, int sign, int dtype, const Var
                 return nullptr;
             }
         } else {
-            v = choose_c32(log2n);
+            v = choose_c32(log2n, n * batch * 8);
         }
         const int tpb = v.wg / (int)(n >> v.log2ept);
         if ((batch + tpb - 1) / tpb > 0x7fffffffLL) {
@@ -1096,8 +1117,15 @@ fft_plan create_nd(int rank, const int64_t* dims, int64_t batch, int sign, int d
     // or for 3D the last two when they fit the single-pass 2D kernel.
     const bool tail2 = rank == 3 && find_nd2(ilog2(dims[1]), ilog2(dims[2]), sign) &&
                        find_nd2(ilog2(dims[1]), ilog2(dims[2]), -sign);
+    const int64_t m = dims[rank - 1];
+    Variant v = choose_c32(ilog2(m), n * batch * 8);
+    const Variant &d = kDefaultC32[11], *force = nullptr;
+    if (m == 2048 && v.log2ept == d.log2ept && v.wg == d.wg && v.kind == d.kind) {
+        v = kLastAxis2048;
+        force = &v;
+    }
     mifft_plan_s* last = tail2 ? create_nd2(dims + 1, batch * dims[0], sign)
-                               : create_batched(dims[rank - 1], batch * (n / dims[rank - 1]), sign, dtype, nullptr);
+                               : create_batched(m, batch * (n / m), sign, dtype, force);
     if (!last)
         return nullptr;
     auto* p = new (std::nothrow) mifft_plan_s();
@@ -1698,7 +1726,7 @@ int fft_plan_query(int64_t n, int64_t batch, int sign, int dtype, fft_plan_desc*
         return ok();
     }
     if (dtype == FFT_R32) {
-        const Variant v = choose_r32(ilog2(n) - 1);
+        const Variant v = choose_r32(ilog2(n) - 1, n * batch * 4);
         if (!find_real(ilog2(n) - 1, v.log2ept, v.wg, sign < 0 ? 0 : 1, v.kind))
             return set_err(FFT_EINVAL_CONFIG, "no real-input kernel compiled for n=%lld", (long long)n);
         fill_desc_r32(n, batch, sign, v, 0, d);
@@ -1716,7 +1744,7 @@ int fft_plan_query(int64_t n, int64_t batch, int sign, int dtype, fft_plan_desc*
         half_query(n, batch, d);
         return ok();
     }
-    const Variant v = choose_c32(ilog2(n));
+    const Variant v = choose_c32(ilog2(n), n * batch * 8);
     if (v.kind == 9 ? !find_fourstep(ilog2(n), 0) : !find_c32(ilog2(n), v.log2ept, v.wg, sign, v.kind))
         return set_err(FFT_EINVAL_CONFIG, "no FP32 kernel compiled for n=%lld", (long long)n);
     fill_desc_c32(n, batch, sign, dtype, v, 0, d);

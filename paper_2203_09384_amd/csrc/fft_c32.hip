@@ -387,11 +387,15 @@ int occupancy_v2()
     return blocks;
 }
 
-// The built-in variant of its length: the one that multidimensional plans
-// run along the last axis, with plain stores.
-constexpr bool is_default(int L, int E, int WG, int kind)
+// Whether multidimensional plans run a variant along the last axis, with
+// plain stores.
+constexpr bool is_last_axis(int L, int E, int WG, int kind)
 {
-    return kDefaultC32[L].log2ept == E && kDefaultC32[L].wg == WG && kDefaultC32[L].kind == kind;
+    auto same = [&](const Variant& v) { return v.log2ept == E && v.wg == WG && v.kind == kind; };
+    for (const SizeRule& r : kRulesC32)
+        if (r.log2 == L && same(r.v))
+            return true;
+    return same(L == 11 ? kLastAxis2048 : kDefaultC32[L]);
 }
 
 // Variant menu, v1: EPT in {2,4,8,16} (not above N; at least 4 once
@@ -447,15 +451,19 @@ void add_v2()
 {
     if constexpr (valid_v2<L, E, WG>()) {
         LaunchC32 feed = nullptr;
-        if constexpr (is_default(L, E, WG, 1 + TW + 2 * PF))
+        if constexpr (is_last_axis(L, E, WG, 1 + TW + 2 * PF))
             feed = &launch_c32_v2<L, E, WG, S, TW, PF, false, true>;
         register_c32(KernelC32{L, E, WG, S, 1 + TW + 2 * PF, &launch_c32_v2<L, E, WG, S, TW, PF, false>,
                                &occupancy_v2<L, E, WG, S, TW, PF, false>, Layout2<L, E>::rows_total(),
                                (WG / ((1 << L) >> E)) * Layout2<L, E>::region() * 8, feed});
-        if constexpr (((1 << L) >> E) <= 64)
+        if constexpr (((1 << L) >> E) <= 64) {
+            feed = nullptr;
+            if constexpr (is_last_axis(L, E, WG, 5 + TW + 2 * PF))
+                feed = &launch_c32_v2<L, E, WG, S, TW, PF, true, true>;
             register_c32(KernelC32{L, E, WG, S, 5 + TW + 2 * PF, &launch_c32_v2<L, E, WG, S, TW, PF, true>,
                                    &occupancy_v2<L, E, WG, S, TW, PF, true>, Layout2<L, E>::rows_total(),
-                                   (WG / ((1 << L) >> E)) * Layout2<L, E>::region() * 8, nullptr});
+                                   (WG / ((1 << L) >> E)) * Layout2<L, E>::region() * 8, feed});
+        }
     }
 }
 
@@ -466,7 +474,7 @@ void add_st()
 {
     if constexpr (LOG2N >= 1 && LOG2N <= 4 && LOG2EPT == LOG2N && WG <= 256) {
         LaunchC32 feed = nullptr;
-        if constexpr (is_default(LOG2N, LOG2EPT, WG, 11))
+        if constexpr (is_last_axis(LOG2N, LOG2EPT, WG, 11))
             feed = &launch_c32_st<LOG2N, WG, S, true>;
         register_c32(KernelC32{LOG2N, LOG2EPT, WG, S, 11, &launch_c32_st<LOG2N, WG, S>, nullptr, 0,
                                WG * ((1 << LOG2N) / 2 + ((1 << LOG2N) >= 4 ? 1 : 0)) * 16, feed});
@@ -481,7 +489,7 @@ void add_st2()
         constexpr int TPT = (1 << L) >> E;
         if constexpr (TPT >= 2 && TPT <= 64 && TPT <= WG) {
             LaunchC32 feed = nullptr;
-            if constexpr (is_default(L, E, WG, 12))
+            if constexpr (is_last_axis(L, E, WG, 12))
                 feed = &launch_c32_st2<L, E, WG, S, true>;
             register_c32(KernelC32{L, E, WG, S, 12, &launch_c32_st2<L, E, WG, S>, nullptr,
                                    Layout2<L, E>::rows_total(),

@@ -3,6 +3,7 @@
 // them up by (log2 N, log2 EPT, workgroup size, sign).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace mifft {
@@ -33,13 +34,50 @@ constexpr Variant kDefaultC32[21] = {
     {4, 128, 12},  // N=256
     {3, 64, 12},   // N=512
     {4, 64, 3},    // N=1024  persistent, next-group prefetch
-    {4, 128, 3},   // N=2048  persistent, next-group prefetch
+    {3, 256, 3},   // N=2048  persistent, next-group prefetch
     {3, 512, 3},   // N=2^12  one transform per workgroup
     {4, 512, 3},   // N=2^13
     {4, 1024, 2},  // N=2^14  135 KiB LDS
     {0, 0, 9},     // N=2^15 .. 2^20: four-step (column + row pass)
     {0, 0, 9}, {0, 0, 9}, {0, 0, 9}, {0, 0, 9}, {0, 0, 9},
 };
+
+// Calls of at most `mib` MiB per direction take `v` instead (the first rule
+// of their length that covers them).  The defaults were picked where the
+// chip is full; below that a persistent grid's workgroups do little more
+// than fill and drain their pipelines, and more, smaller threads per
+// transform finish sooner.  MI355X, us, default -> rule (three buffer sets
+// in turn):
+//   N=256   0.5 MiB 3.4 -> 2.9, 8 MiB 5.0 -> 4.5, 32 MiB 13.9 -> 13.4 (64: 24.1 -> 25.5)
+//   N=512   0.5 MiB 2.9 -> 2.7, 8 MiB 4.6 -> 4.2, 16 MiB 7.3 -> 6.7 (40: 15.9 -> 17.2)
+//   N=1024  8 MiB 6.1 -> 4.8, 16 MiB 10.2 -> 7.0, 24 MiB 11.5 -> 9.6 (40: 17.1 -> 19.0);
+//           64 MiB 25.9 -> 24.8, 128 MiB 47.6 -> 46.4 (512: 182 -> 184)
+//   N=2048  8 MiB 5.3 -> 4.9, 16 MiB 8.7 -> 7.8, 24 MiB 12.0 -> 11.6 (32: 14.6 -> 15.2)
+//   N=2^12  0.5 MiB 5.0 -> 4.3, 16 MiB 8.8 -> 8.0 (40: 16.6 -> 19.6)
+//   N=2^13  0.5 MiB 8.4 -> 7.8, 16 MiB 13.1 -> 12.0, 32 MiB 17.8 -> 16.5 (40: 23.5 -> 24.5)
+struct SizeRule {
+    int log2;  // of the length (FFT_R32: of the half length)
+    int mib;
+    Variant v;
+};
+constexpr SizeRule kRulesC32[] = {
+    {8, 32, {3, 64, 6}},   {9, 16, {3, 64, 6}},   {10, 24, {3, 128, 2}}, {10, 128, {3, 256, 3}},
+    {11, 24, {3, 256, 2}}, {12, 16, {3, 512, 2}}, {13, 32, {4, 512, 2}},
+};
+
+// The last axis of a multidimensional plan, storing plainly for the next
+// pass, keeps 16 points per thread at 2048 points (2D 2048 x 2048 x 16, 16
+// against 8 points: 374 against 380 us; plain calls 183.4 against 181.2).
+constexpr Variant kLastAxis2048{4, 128, 3};
+
+template <size_t N>
+constexpr Variant rule_or(const SizeRule (&rules)[N], int log2, int64_t bytes, Variant otherwise)
+{
+    for (const SizeRule& r : rules)
+        if (r.log2 == log2 && bytes <= (int64_t(r.mib) << 20))
+            return r.v;
+    return otherwise;
+}
 
 struct KernelC32 {
     int log2n, log2ept, wg, sign;
@@ -51,8 +89,8 @@ struct KernelC32 {
     int rows;                 // twiddle-row entries the variant needs (kind >= 1)
     int lds_bytes;            // LDS per workgroup
     // the same with plain stores, which stay in the memory-side cache for the
-    // next pass of a multidimensional transform; compiled for the built-in
-    // variant of each length, else NULL
+    // next pass of a multidimensional transform; compiled for the
+    // variants that those run, else NULL
     LaunchC32 feed;
 };
 
