@@ -39,6 +39,7 @@ def _units():
     for L in range(0, 15):
         units.append(("real.hip", f"real_M{L}.o", [f"-DMIFFT_LOG2M={L}"]))
     units.append(("twiddle.hip", "twiddle.o", []))
+    units.append(("scale.hip", "scale.o", []))
     units.append(("fourstep.hip", "fourstep.o", []))
     units.append(("nd.hip", "nd.o", []))
     units.append(("nd2.hip", "nd2.o", []))

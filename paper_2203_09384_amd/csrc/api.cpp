@@ -226,25 +226,6 @@ constexpr SizeRule kRulesR32[] = {
     {10, 96, {3, 256, 3}},  {11, 32, {3, 256, 2}}, {12, 32, {3, 512, 2}},
 };
 
-// Fused loss-gradient kernel (two transforms per group, so its own best
-// shape differs from the plain transform's), per log2 N (index 1..11):
-// the autotuner's pick on MI355X at 2^25 elements (log2 EPT, workgroup
-// size; the kind field is unused).
-const Variant kDefaultLoss[12] = {
-    {0, 0, 0},     // unused
-    {1, 128, 0},   // N=2
-    {2, 64, 0},    // N=4
-    {3, 256, 0},   // N=8
-    {2, 64, 0},    // N=16
-    {2, 256, 0},   // N=32
-    {2, 256, 0},   // N=64
-    {3, 256, 0},   // N=128
-    {4, 64, 0},    // N=256
-    {3, 256, 0},   // N=512
-    {4, 256, 0},   // N=1024
-    {4, 128, 0},   // N=2048
-};
-
 std::once_flag g_tune_once;
 Variant g_tuned_c32[21];
 bool g_have_tuned_c32[21];

@@ -12,6 +12,7 @@
 #include "device_fft.hpp"
 #include "launch.hpp"
 #include "fused_loss.hpp"
+#include "stream.hpp"
 
 #ifndef MIFFT_LOG2N
 #error "compile with -DMIFFT_LOG2N=<1..11>"
@@ -102,7 +103,7 @@ __device__ __forceinline__ void forward_passes(cf (&v)[1 << E], int t, const cf*
 // One group: loss and gradient of the transforms in `v`.  With PF the
 // next group `gn` is loaded into `nx` during the forward passes; the
 // weights are read first, so that their wait does not cover those loads.
-template <int L, int E, int WG, int S, bool PF>
+template <int L, int E, int WG, int S, bool PLAIN, bool PF>
 __device__ __forceinline__ void loss_grad_group(cf (&v)[1 << E], cf (&nx)[1 << E], const cf* __restrict__ x,
                                                 int64_t gn, const float* __restrict__ w,
                                                 cf* __restrict__ grad, float* __restrict__ loss,
@@ -159,14 +160,20 @@ __device__ __forceinline__ void loss_grad_group(cf (&v)[1 << E], cf (&nx)[1 << E
             lds_sync<WAVE>();  // the forward's last exchange is fully read
     }
     transform_passes<L, E, -S>(v, t, rows, lds);  // A^H g (before its scale)
-    store_group<L, E, TPB>(v, grad, g, batch, tb, toff8, scale);
+    store_group<L, E, TPB, PLAIN>(v, grad, g, batch, tb, toff8, scale);
     if constexpr (TPT > 1)
         lds_sync<WAVE>();  // LDS is reused by the next group
 }
 
+// PLAIN: the gradient stays in the memory-side cache, where the backward,
+// which scales it, finds it.  That pays while the whole gradient fits
+// (kChunkBytes): forward + backward at N = 2048, MI355X, nontemporal -> plain,
+// 256 MiB 216 -> 195 us, 128 MiB 113 -> 109, 512 MiB 422 -> 444.  Compiled
+// for the built-in shapes.
+//
 // Persistent: workgroups walk transform groups, loading the next group's x
 // while the current one is processed.
-template <int L, int E, int WG, int S>
+template <int L, int E, int WG, int S, bool PLAIN>
 __global__ __launch_bounds__(WG) void k_fft_loss_grad(const cf* __restrict__ x, const float* __restrict__ w,
                                                       cf* __restrict__ grad, float* __restrict__ loss,
                                                       const cf* __restrict__ rows, int64_t batch, float scale)
@@ -191,7 +198,7 @@ __global__ __launch_bounds__(WG) void k_fft_loss_grad(const cf* __restrict__ x, 
     // before the current group's first use cover the prefetch too) and
     // spread over the forward passes.
     int64_t left = (ngroups - 1 - g) / stride;
-#define LG(PF, V, NX, GN) loss_grad_group<L, E, WG, S, PF>(V, NX, x, GN, w, grad, loss, rows, g, batch, tb, t, toff8, scale, my, red)
+#define LG(PF, V, NX, GN) loss_grad_group<L, E, WG, S, PLAIN, PF>(V, NX, x, GN, w, grad, loss, rows, g, batch, tb, t, toff8, scale, my, red)
     while (left >= 2) {
         LG(true, a, b, g + stride);
         g += stride;
@@ -217,16 +224,18 @@ hipError_t launch_loss_grad(const void* x, const float* w, void* grad, float* lo
     int64_t grid = (batch + TPB - 1) / TPB;
     if (grid_limit > 0 && grid > grid_limit)
         grid = grid_limit;
-    return launch_kernel((k_fft_loss_grad<L, E, WG, S>), dim3((unsigned)grid), dim3(WG), 0, stream,
-                       static_cast<const cf*>(x), w, static_cast<cf*>(grad), loss, static_cast<const cf*>(rows),
-                       batch, scale);
+    constexpr bool builtin = kDefaultLoss[L].log2ept == E && kDefaultLoss[L].wg == WG;
+    const bool plain = builtin && batch * (int64_t(8) << L) <= kChunkBytes;
+    return launch_kernel(plain ? k_fft_loss_grad<L, E, WG, S, builtin> : k_fft_loss_grad<L, E, WG, S, false>,
+                         dim3((unsigned)grid), dim3(WG), 0, stream, static_cast<const cf*>(x), w,
+                         static_cast<cf*>(grad), loss, static_cast<const cf*>(rows), batch, scale);
 }
 
 template <int L, int E, int WG, int S>
 int occupancy_loss_grad()
 {
     int blocks = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_fft_loss_grad<L, E, WG, S>, WG, 0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_fft_loss_grad<L, E, WG, S, false>, WG, 0) != hipSuccess)
         return 0;
     return blocks;
 }

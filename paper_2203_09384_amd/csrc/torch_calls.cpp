@@ -37,6 +37,7 @@ struct Calls {
     int (*adjoint)(fft_plan, const void*, void*, void*) = nullptr;
     int (*loss_grad)(fft_plan, const void*, const float*, void*, float*, void*) = nullptr;
     int (*scaled)(fft_plan, const void*, const int32_t*, void*, int32_t*, void*) = nullptr;
+    int (*scale)(const void*, const float*, void*, int64_t, void*) = nullptr;
     void (*destroy)(fft_plan) = nullptr;
     PyObject* check = nullptr;
 };
@@ -103,10 +104,23 @@ Plan* plan_of(PyObject* o)
     throw e;
 }
 
+// Nothing that would see this call otherwise than as a kernel launch.
+bool plain_context()
+{
+    return !c10::impl::TorchDispatchModeTLS::any_modes_set() && at::impl::PythonTorchFunctionTLS::stack_len() == 0 &&
+           !c10::impl::tls_is_dispatch_key_included(c10::DispatchKey::FuncTorchDynamicLayerFrontMode) &&
+           !torch::jit::tracer::isTracing();
+}
+
+bool dense(const Tensor& t, at::ScalarType type)
+{
+    return t.is_cuda() && t.layout() == at::kStrided && t.has_storage() && t.is_contiguous() && !t.is_conj() && !t.is_neg() &&
+           t.scalar_type() == type;
+}
+
 bool side_ok(const Tensor& t, const PlanRef& p, bool input, bool adj)
 {
-    return t.is_cuda() && t.layout() == at::kStrided && t.is_contiguous() && !t.is_conj() && !t.is_neg() &&
-           t.scalar_type() == p.type(input, adj) && t.numel() == p.values(input, adj) * p.batch;
+    return dense(t, p.type(input, adj)) && t.numel() == p.values(input, adj) * p.batch;
 }
 
 // Whether a call without an output given has one of the plan's shape.
@@ -181,20 +195,20 @@ struct LossFn : torch::autograd::Function<LossFn> {
     static torch::autograd::tensor_list backward(torch::autograd::AutogradContext* ctx,
                                                  torch::autograd::tensor_list grads)
     {
-        const Tensor grad = ctx->get_saved_variables()[0];
-        return {grad * grads[0].to(at::kFloat), Tensor(), Tensor()};
+        const Tensor grad = ctx->get_saved_variables()[0], g = grads[0].to(at::kFloat);
+        // a plain product of what forward saved, with no graph of its own
+        if (plain_context() && !(at::GradMode::is_enabled() && g.requires_grad()) && dense(grad, at::kComplexFloat) &&
+            dense(g, at::kFloat) && g.numel() == 1 && g.device() == grad.device() && grad.numel() > 0) {
+            Tensor out = at::empty_like(grad);
+            if (g_calls.scale(grad.data_ptr(), static_cast<const float*>(g.data_ptr()), out.data_ptr(), grad.numel(),
+                              c10::hip::getCurrentHIPStream().stream()) == 0)
+                return {out, Tensor(), Tensor()};
+        }
+        return {grad * g, Tensor(), Tensor()};
     }
 };
 
 // ------------------------------------------------------------------ Python
-// Nothing that would see this call otherwise than as a kernel launch.
-bool plain_context()
-{
-    return !c10::impl::TorchDispatchModeTLS::any_modes_set() && at::impl::PythonTorchFunctionTLS::stack_len() == 0 &&
-           !c10::impl::tls_is_dispatch_key_included(c10::DispatchKey::FuncTorchDynamicLayerFrontMode) &&
-           !torch::jit::tracer::isTracing();
-}
-
 const Tensor* plain_tensor(PyObject* o)
 {
     if (!THPVariable_CheckExact(o))
@@ -379,8 +393,7 @@ PyObject* py_loss(PyObject*, PyObject* const* a, Py_ssize_t n)
         Plan* plan = cached(a[0], *xp, (int)sign, c32, 0, 0);
         if (!plan || (*plan)->n > 2048 || !side_ok(*xp, **plan, true, false))
             return not_implemented();
-        if (!wp->is_cuda() || wp->layout() != at::kStrided || !wp->is_contiguous() || wp->is_neg() ||
-            wp->scalar_type() != at::kFloat || wp->numel() != xp->numel())
+        if (!dense(*wp, at::kFloat) || wp->numel() != xp->numel())
             return not_implemented();
         const Plan keep = *plan;
         const Tensor x = *xp, w = *wp;
@@ -420,17 +433,18 @@ PyObject* py_scaled(PyObject*, PyObject* const* a, Py_ssize_t n)
     });
 }
 
-// bind(execute, adjoint, loss_grad, scaled, destroy, check)
+// bind(execute, adjoint, loss_grad, scaled, scale, destroy, check)
 PyObject* py_bind(PyObject*, PyObject* args)
 {
-    unsigned long long e, d, l, s, x;
+    unsigned long long e, d, l, s, c, x;
     PyObject* check;
-    if (!PyArg_ParseTuple(args, "KKKKKO", &e, &d, &l, &s, &x, &check))
+    if (!PyArg_ParseTuple(args, "KKKKKKO", &e, &d, &l, &s, &c, &x, &check))
         return nullptr;
     g_calls.execute = reinterpret_cast<decltype(g_calls.execute)>(e);
     g_calls.adjoint = reinterpret_cast<decltype(g_calls.adjoint)>(d);
     g_calls.loss_grad = reinterpret_cast<decltype(g_calls.loss_grad)>(l);
     g_calls.scaled = reinterpret_cast<decltype(g_calls.scaled)>(s);
+    g_calls.scale = reinterpret_cast<decltype(g_calls.scale)>(c);
     g_calls.destroy = reinterpret_cast<decltype(g_calls.destroy)>(x);
     Py_INCREF(check);
     g_calls.check = check;

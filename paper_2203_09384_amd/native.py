@@ -133,7 +133,7 @@ def calls():
         loader.exec_module(m)
         m.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in
                  (L.fft_execute, L.fft_execute_adjoint, L.fft_execute_loss_grad, L.fft_execute_scaled,
-                  L.fft_plan_destroy)), check)
+                  L.mifft_scale_c32, L.fft_plan_destroy)), check)
         _calls = m
     return _calls
 

@@ -125,3 +125,35 @@ def test_closed_plan_is_refused():
     p.close()
     with pytest.raises(MifftError):
         p.execute(rand(8, 64))
+
+
+@pytest.mark.parametrize("batch,n", [(1, 2), (1, 4), (3, 64), (16385, 2048)])
+@pytest.mark.parametrize("factor", [1.0, -2.5, float("inf"), float("nan")])
+def test_loss_backward_scales_like_torch(batch, n, factor):
+    """The scaling kernel against torch's product, at odd and even point
+    counts, above the size at which it streams, and for factors that are not
+    finite: bit for bit."""
+    x = rand(batch, n).requires_grad_(True)
+    w = torch.rand(batch, n, device="cuda")
+    f = torch.tensor(factor, device="cuda")
+    api.weighted_power_loss(x, w)
+    loss = api.weighted_power_loss(x, w)
+    _, unit = api.get_plan(n, batch, -1, "c32", 0).loss_grad(x.detach(), w)
+    (got,) = torch.autograd.grad(loss, x, f)
+    want = unit * f
+    assert torch.equal(torch.view_as_real(got).view(torch.int32) if factor == factor else torch.view_as_real(got).isnan(),
+                       torch.view_as_real(want).view(torch.int32) if factor == factor else torch.view_as_real(want).isnan())
+
+
+def test_loss_gradient_of_gradient_and_batched():
+    """A backward that is itself differentiated, or run under vmap, keeps
+    torch's own product."""
+    x, w = rand(4, 64).requires_grad_(True), torch.rand(4, 64, device="cuda")
+    api.weighted_power_loss(x, w)
+    g = torch.tensor(2.0, device="cuda", requires_grad=True)
+    (grad,) = torch.autograd.grad(api.weighted_power_loss(x, w), x, g, create_graph=True)
+    (gg,) = torch.autograd.grad(grad.real.sum(), g)
+    assert torch.allclose(gg, grad.real.sum() / 2)
+    several = torch.autograd.grad(api.weighted_power_loss(x, w), x, torch.tensor([1.0, 3.0], device="cuda"),
+                                  is_grads_batched=True)[0]
+    assert torch.equal(several[1], 3 * several[0])
