@@ -78,6 +78,9 @@ constexpr bool nd2_persistent()
            Z::LDS + (RW::R0 + RW::R1) * 8 <= 160 * 1024 && Z::EPT % Sched<L0, Z::E>::NP == 0 && L1 < 10;
 }
 
+// (Twiddle rows read after the exchanges, as run2 does without AHEAD: read
+// ahead, 64 x 64 went 206 -> 202 us at 2^26 points, but 128 x 64 218 -> 222 and
+// one array of 64 x 64 5.2 -> 5.4.)
 template <int L0, int L1, int S>
 __global__ __launch_bounds__((Nd2Shape<L0, L1>::WG)) void k_nd2(const cf* __restrict__ in, cf* __restrict__ out,
                                                              const cf* __restrict__ rows0,
@@ -104,7 +107,7 @@ __global__ __launch_bounds__((Nd2Shape<L0, L1>::WG)) void k_nd2(const cf* __rest
 #pragma unroll
         for (int m = 0; m < EPT; m++)
             v[m] = live ? src[t + m * Z::TPT1] : cf{0.f, 0.f};
-        run2<L1, E, S, 1, true>(v, t, rows1, tw1, my + r * Z::RS1);
+        run2<L1, E, S, 1, true, 0, 0, false>(v, t, rows1, tw1, my + r * Z::RS1);
         __syncthreads();  // every row's exchanges are read
 #pragma unroll
         for (int m = 0; m < EPT; m++)
@@ -125,7 +128,7 @@ __global__ __launch_bounds__((Nd2Shape<L0, L1>::WG)) void k_nd2(const cf* __rest
         v[m] = col[t0 + m * Z::TPT0];
     if constexpr (Z::TPT0 > 1)
         __syncthreads();  // the column is read before its exchanges overwrite it
-    run2<L0, E, S, 1, false>(v, t0, rows0, tw0, col);
+    run2<L0, E, S, 1, false, 0, 0, false>(v, t0, rows0, tw0, col);
     if (live) {
         cf* dst = out + arr * N + c;
 #pragma unroll
