@@ -1261,7 +1261,13 @@ int exec_nd(fft_plan p, const void* in, void* out, int sign, hipStream_t st)
         return k->fn(dst + off, p->ax_rows[a], points / p->dims[a], p->ax_log2s[a], p->ax_scale[a], stream && a == 0, st);
     };
     const int64_t n = p->n, unit = p->ax_first == 1 ? n / p->dims[0] : n;  // of the first two passes
-    const int64_t outer = stream ? chunk_units(n * (int64_t)sizeof(float2)) : p->batch;
+    // The single-pass 2D kernel reads plainly (its rows are half lines to a
+    // wavefront), so its input takes cache as well: half the chunk (MI355X,
+    // 512 MiB, 256 -> 128 MiB: 128^3 409 -> 400 us, 256 x 64 x 64 398 -> 384,
+    // 512 x 64 x 128 415 -> 391; 512 x 512, whose first pass reads
+    // nontemporally, 314 -> 329).
+    const int64_t cost = n * (int64_t)sizeof(float2) * (p->last->nd2_same ? 2 : 1);
+    const int64_t outer = stream ? chunk_units(cost) : p->batch;
     for (int64_t b = 0; b < p->batch; b += outer) {
         const int64_t off = b * n, points = std::min(outer, p->batch - b) * n;
         const int64_t step = stream && p->ax_first == 1 ? chunk_units(unit * (int64_t)sizeof(float2)) * unit : points;
