@@ -19,6 +19,7 @@
 #include "launch.hpp"
 #include "nd2.hpp"
 #include "nd_maps.hpp"
+#include "stream.hpp"
 
 #include <utility>
 
@@ -81,7 +82,7 @@ constexpr bool nd2_persistent()
 // (Twiddle rows read after the exchanges, as run2 does without AHEAD: read
 // ahead, 64 x 64 went 206 -> 202 us at 2^26 points, but 128 x 64 218 -> 222 and
 // one array of 64 x 64 5.2 -> 5.4.)
-template <int L0, int L1, int S>
+template <int L0, int L1, int S, bool NT>
 __global__ __launch_bounds__((Nd2Shape<L0, L1>::WG)) void k_nd2(const cf* __restrict__ in, cf* __restrict__ out,
                                                              const cf* __restrict__ rows0,
                                                              const cf* __restrict__ rows1, int64_t batch, float scale)
@@ -133,7 +134,7 @@ __global__ __launch_bounds__((Nd2Shape<L0, L1>::WG)) void k_nd2(const cf* __rest
         cf* dst = out + arr * N + c;
 #pragma unroll
         for (int m = 0; m < EPT; m++)
-            dst[(t0 + m * Z::TPT0) * N1] = cscale(v[m], scale);
+            st_data<NT>(reinterpret_cast<char*>(dst + (t0 + m * Z::TPT0) * N1), cscale(v[m], scale));
     }
 }
 
@@ -145,7 +146,7 @@ __global__ __launch_bounds__((Nd2Shape<L0, L1>::WG)) void k_nd2(const cf* __rest
 // loads in the loop are the arrays themselves.  The loop body always
 // prefetches; the last array runs after it without (a prefetch under a
 // condition would make the wait for the next rows cover the stores too).
-template <int L0, int L1, int S>
+template <int L0, int L1, int S, bool NT>
 __global__ __launch_bounds__((Nd2Shape<L0, L1>::WG)) void k_nd2p(const cf* __restrict__ in, cf* __restrict__ out,
                                                               const cf* __restrict__ rows0,
                                                               const cf* __restrict__ rows1, int64_t batch, float scale)
@@ -206,7 +207,7 @@ __global__ __launch_bounds__((Nd2Shape<L0, L1>::WG)) void k_nd2p(const cf* __res
         cf* dst = out + g * N + c;
 #pragma unroll
         for (int m = 0; m < EPT; m++)
-            dst[(t0 + m * Z::TPT0) * N1] = cscale(v[m], scale);
+            st_data<NT>(reinterpret_cast<char*>(dst + (t0 + m * Z::TPT0) * N1), cscale(v[m], scale));
     };
     // The loop is rotated (rows of the next array at the end of the body), so
     // the prefetched rows are used in the body that loaded them and the wait
@@ -243,7 +244,7 @@ int nd2_slots()
     if (cached[dev] == 0) {
         int cus = 0, per = 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_nd2p<L0, L1, S>, Nd2Shape<L0, L1>::WG, 0) !=
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_nd2p<L0, L1, S, false>, Nd2Shape<L0, L1>::WG, 0) !=
                 hipSuccess)
             return 0;
         cached[dev] = cus * per;
@@ -265,17 +266,23 @@ hipError_t launch_nd2(const void* in, void* out, const void* rows0, const void* 
                       hipStream_t stream)
 {
     using Z = Nd2Shape<L0, L1>;
+    // Outputs beyond the memory-side cache leave nontemporally where a
+    // wavefront's store covers at least half lines (MI355X, 512 MiB, plain ->
+    // nontemporal: 128 x 128 221.6 -> 213.8 us, 256 x 16 200 -> 192, 16 x 16
+    // 279 -> 258, 8 x 8 214 -> 211, but 4 x 4 179 -> 366).
+    constexpr bool NT = Z::N1 >= 8;
+    const bool nt = NT && batch * (int64_t)(Z::N * sizeof(cf)) > kChunkBytes;
     if constexpr (nd2_persistent<L0, L1>()) {
         const int slots = nd2_slots<L0, L1, S>();
         if (slots > 0) {
             const int64_t grid = batch > slots ? slots : batch;
-            return launch_kernel((k_nd2p<L0, L1, S>), dim3((unsigned)grid), dim3(Z::WG), 0, stream,
+            return launch_kernel(nt ? k_nd2p<L0, L1, S, NT> : k_nd2p<L0, L1, S, false>, dim3((unsigned)grid), dim3(Z::WG), 0, stream,
                                  static_cast<const cf*>(in), static_cast<cf*>(out), static_cast<const cf*>(rows0),
                                  static_cast<const cf*>(rows1), batch, scale);
         }
     }
     const int64_t grid = (batch + Z::AP - 1) / Z::AP;
-    return launch_kernel((k_nd2<L0, L1, S>), dim3((unsigned)grid), dim3(Z::WG), 0, stream,
+    return launch_kernel(nt ? k_nd2<L0, L1, S, NT> : k_nd2<L0, L1, S, false>, dim3((unsigned)grid), dim3(Z::WG), 0, stream,
                        static_cast<const cf*>(in), static_cast<cf*>(out), static_cast<const cf*>(rows0),
                        static_cast<const cf*>(rows1), batch, scale);
 }

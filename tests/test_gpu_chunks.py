@@ -46,3 +46,18 @@ def test_nd_chunks(shape, batch, sign):
     for b in {0, batch - 1}:
         ref = oracle.fftn(to_cpu(x[b:b + 1]).astype(np.complex128), len(shape), sign, 1.0 if sign < 0 else 1.0 / n)
         assert per_transform_relerr(to_cpu(y[b]).reshape(1, -1), ref.reshape(1, -1)) <= TOL
+
+
+@pytest.mark.parametrize("shape", [(4, 4), (8, 8), (16, 16), (64, 64), (128, 128), (8, 8, 8), (16, 16, 16), (4, 8, 64)],
+                         ids=str)
+@pytest.mark.parametrize("sign", [-1, 1])
+def test_single_pass_nd_beyond_the_cache(shape, sign):
+    """Single-pass 2D / 3D transforms whose output exceeds 256 MiB."""
+    n = int(np.prod(shape))
+    batch = (257 << 17) // n + 1
+    x = signal(batch, *shape)
+    print(f"[case] nd beyond the cache shape={shape} batch={batch} sign={sign}", flush=True)
+    y = api.PlanND(shape, batch, sign).execute(x)
+    at = torch.tensor([0, 1, batch // 2, batch - 1], device="cuda")
+    ref = oracle.fftn(to_cpu(x[at]).astype(np.complex128), len(shape), sign, 1.0 if sign < 0 else 1.0 / n)
+    assert per_transform_relerr(to_cpu(y[at]).reshape(4, -1), ref.reshape(4, -1)) <= TOL
