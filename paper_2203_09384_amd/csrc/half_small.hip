@@ -4,11 +4,16 @@
 //
 // Storage is (re, im) pairs of 16-bit values with one int32 exponent per
 // transform (logical value = stored * 2^exp).  Each transform is
-//   loaded and widened to FP32, scaled by the power of two that brings its
-//   largest component into [1/2, 1) (exact), transformed with the FP32
-//   passes (growth at most N <= 2^10), scaled again so its largest output
+//   loaded and widened to FP32, scaled (BF16) by the power of two that
+//   brings its largest component into [1/2, 1) (exact), transformed with the
+//   FP32 passes (growth at most N <= 2^10), scaled so its largest output
 //   component lies in [2^14, 2^15) (exact), and narrowed to the storage
 //   type once.
+// At 16 bits a point brings half the bytes of FP32 for the same arithmetic,
+// so from 32 points up the conversions and scalings around the passes show.
+// MI355X, 256 MiB, FP16, input scaling and single converts -> none and packed
+// ones: N = 32 107.8 -> 101.1 us, 512 104.3 -> 99.0, 1024 120.8 -> 112.0;
+// BF16 (packed converts only) 108.9 -> 107.4, 102.1 -> 101.1, 118.3 -> 115.0.
 // out_exp = in_exp + e_in + e_out - 15 (- log2 N for the inverse's 1/N).
 // The radix-16 MFMA passes of the 2048-point kernel need at least 256
 // points and pay off at that size; here the transform's threads share one
@@ -38,13 +43,25 @@ __device__ __forceinline__ float h_to_f32(uint32_t h)
         return (float)__builtin_bit_cast(_Float16, (uint16_t)h);
 }
 
+typedef float v2f32 __attribute__((ext_vector_type(2)));
+typedef _Float16 v2f16 __attribute__((ext_vector_type(2)));
+typedef __bf16 v2bf16 __attribute__((ext_vector_type(2)));
+
+// (re, im) narrowed to nearest even in one packed convert.
 template <bool BF>
-__device__ __forceinline__ uint32_t f32_to_h(float f)
+__device__ __forceinline__ uint32_t pack_h(cf y)
 {
+    const v2f32 f{y.x, y.y};
     if constexpr (BF)
-        return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)f);
+        return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, v2bf16));
     else
-        return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)f);
+        return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, v2f16));
+}
+
+template <bool BF>
+__device__ __forceinline__ cf unpack_h(uint32_t u)
+{
+    return cf{h_to_f32<BF>(u & 0xffffu), h_to_f32<BF>(u >> 16)};
 }
 
 // Largest |component| over the TPT threads of a transform (contiguous
@@ -149,35 +166,62 @@ __device__ __forceinline__ void small_group(const uint32_t* __restrict__ in, con
 #pragma unroll
         for (int m = 0; m < EPT; m++) {
             const uint32_t u = blk[tb * ROWW + t + m * TPT];
-            v[m] = cf{h_to_f32<BF>(u & 0xffffu), h_to_f32<BF>(u >> 16)};
+            v[m] = unpack_h<BF>(u);
         }
     } else {
 #pragma unroll
         for (int m = 0; m < EPT; m++) {
             const uint32_t u = live ? in[b * N + t + m * TPT] : 0u;
-            v[m] = cf{h_to_f32<BF>(u & 0xffffu), h_to_f32<BF>(u >> 16)};
+            v[m] = unpack_h<BF>(u);
         }
     }
-    // normalise: largest component into [1/2, 1), as an exponent shift of
-    // each value (exact, and no overflow of a 2^-e_in factor when the
-    // largest component is near the bottom of the format's range)
-    const int e_in = exp_above(group_max<TPT>(abs_max<E>(v)));
+    // BF16: normalise, largest component into [1/2, 1), as an exponent shift
+    // of each value (exact, and no overflow of a 2^-e_in factor when the
+    // largest component is near the bottom of the format's range).  FP16
+    // needs none: its values times the passes' growth stay far inside FP32's
+    // range, where a power of two changes no rounding, so the results are
+    // the same bit for bit.
+    int e_in = 0;
+    if constexpr (BF) {
+        e_in = exp_above(group_max<TPT>(abs_max<E>(v)));
 #pragma unroll
-    for (int m = 0; m < EPT; m++)
-        v[m] = cf{ldexpf(v[m].x, -e_in), ldexpf(v[m].y, -e_in)};
+        for (int m = 0; m < EPT; m++)
+            v[m] = cf{ldexpf(v[m].x, -e_in), ldexpf(v[m].y, -e_in)};
+    }
     if constexpr (TPT == 1)
         pass_compute2<L, E, S, 0>(v, tws[0]);
     else
         run2<L, E, S, TW, true>(v, t, rows, tws, lds + tb * REG);
     // output: largest component into [2^14, 2^15), or the logical value
-    const int e_o = exp_above(group_max<TPT>(abs_max<E>(v)));
+    const float top = group_max<TPT>(abs_max<E>(v));
+    const int e_o = exp_above(top);
+    if constexpr (!BF) {
+        // No finite output component but zero: a transform of zeros, or of
+        // NaN alone, whose exponent is that of its largest input.
+        if (top == 0.f) {
+            cf x[EPT];
+#pragma unroll
+            for (int m = 0; m < EPT; m++)
+                x[m] = unpack_h<BF>(STAGED ? blk[tb * ROWW + t + m * TPT] : live ? in[b * N + t + m * TPT] : 0u);
+            e_in = exp_above(group_max<TPT>(abs_max<E>(x)));
+        }
+    }
     const int ein = (live && in_exp) ? in_exp[b] : 0;
     const int e_total = ein + e_in + e_o - 15 + scale_log2;  // logical = stored * 2^e_total
+    if (out_exp) {
+        // e_o is at least -60, so the factor is a normal number and exact
+        const float f = ldexpf(1.f, 15 - e_o);
+#pragma unroll
+        for (int m = 0; m < EPT; m++)
+            v[m] = cscale(v[m], f);
+    } else {
+#pragma unroll
+        for (int m = 0; m < EPT; m++)
+            v[m] = cf{ldexpf(v[m].x, ein + e_in + scale_log2), ldexpf(v[m].y, ein + e_in + scale_log2)};
+    }
 #pragma unroll
     for (int m = 0; m < EPT; m++) {
-        const cf y = out_exp ? cf{ldexpf(v[m].x, 15 - e_o), ldexpf(v[m].y, 15 - e_o)}
-                             : cf{ldexpf(v[m].x, ein + e_in + scale_log2), ldexpf(v[m].y, ein + e_in + scale_log2)};
-        const uint32_t u = f32_to_h<BF>(y.x) | (f32_to_h<BF>(y.y) << 16);
+        const uint32_t u = pack_h<BF>(v[m]);
         if constexpr (STAGED)
             blk[tb * ROWW + t + m * TPT] = u;  // this thread's own elements: no other thread reads them yet
         else if (live)
