@@ -79,7 +79,7 @@ def kernel_name(d):
     v = d["variant"] - 1
     wave = v >= 4
     v %= 4
-    return f"k_fft_c32_v2<{L}, {e}, {d['wg']}, {d['sign']}, {v % 2}, {v // 2}, {str(wave).lower()}>"
+    return f"k_fft_c32_v2<{L}, {e}, {d['wg']}, {d['sign']}, {v % 2}, {v // 2}, {str(wave).lower()}, false>"
 
 
 def time_launches(fn, steps, warmup, torch):
