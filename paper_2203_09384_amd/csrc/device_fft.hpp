@@ -636,8 +636,10 @@ __device__ __forceinline__ void load_all_rows(TwRegs<L, E>& tws, const cf* __res
 // read from `rows`, with AHEAD each pass's before the exchange that precedes
 // it, so that the read and the exchange overlap (MI355X, read after -> before
 // the exchange: 2^14 at 512 MiB 276 -> 267 us, two transforms 13.0 -> 11.8;
-// real 2^15 349 -> 327; 3D 4 x 4 x 64 181 -> 174).  `w` holds the row of
-// pass P > 0.
+// real 2^15 349 -> 327; 3D 4 x 4 x 64 181 -> 174).  A second row held over
+// the exchange costs registers, so it pays where few wavefronts share a SIMD
+// and one's exchange has nothing beside it; callers whose wavefronts cover
+// for each other read after it.  `w` holds the row of pass P > 0.
 template <int L, int E, int S, int TW, bool WAVE, int P, int PAD, bool AHEAD>
 __device__ __forceinline__ void run2_from(cf (&v)[1 << E], int t, const cf* __restrict__ rows,
                                           const TwRegs<L, E>& tws, cf* lds, const cf (&w)[1 << E])

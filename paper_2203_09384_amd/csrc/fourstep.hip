@@ -112,7 +112,8 @@ __global__ __launch_bounds__(TILE*((1 << L1) >> inner_e(L1))) void k_fourstep1(
     TwRegs<L1, E> tws;
     unit_rows<L1, E>(tws);
     constexpr bool WAVE = DIRECT ? TPT * T <= 64 : TPT <= 64;
-    run2<L1, E, S, 1, WAVE>(v, t, rows, tws, my);
+    // rows after the exchange: enough wavefronts (2^16 at 16 MiB 19.3, ahead 19.5)
+    run2<L1, E, S, 1, WAVE, 0, 0, false>(v, t, rows, tws, my);
     const unsigned n2 = nb * T + tb;
 #pragma unroll
     for (int m = 0; m < EPT; m++) {

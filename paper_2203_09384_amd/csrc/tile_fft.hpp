@@ -82,7 +82,8 @@ __device__ __forceinline__ void axis_tile_staged(cf* __restrict__ io, const cf* 
         v[m] = my[t + m * TPT];
     TwRegs<L, E> tws;
     unit_rows<L, E>(tws);
-    run2<L, E, S, 1, WAVE>(v, t, rows, tws, my);
+    // rows after the exchange: enough wavefronts (2^16 at 16 MiB 19.3, ahead 19.5)
+    run2<L, E, S, 1, WAVE, 0, 0, false>(v, t, rows, tws, my);
     if constexpr (TPT > 1)
         lds_sync<WAVE>();  // the last exchange is fully read
 #pragma unroll
