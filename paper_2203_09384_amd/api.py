@@ -5,10 +5,13 @@ the HIP kernels of libmifft.so; torch provides device memory and streams.
 The ordinary case of each call (plain dense GPU tensors of the plan's type
 and size, the current stream) is made in C++ (csrc/torch_calls.cpp), which
 returns NotImplemented for anything else; the code here then handles or
-refuses it.
+refuses it.  Lazily conjugated or negated tensors (x.conj()) hold other
+values than they show: the calls here resolve such inputs and gradients, and
+fill such outputs with a copy.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import threading
 
@@ -28,6 +31,37 @@ def _stream_handle(stream=None):
 
 def _ptr(t):
     return ctypes.c_void_p(t.data_ptr())
+
+
+def _is_lazy(t):
+    # (one that is not contiguous either is refused as such)
+    return t is not None and (t.is_conj() or t.is_neg()) and t.is_contiguous()
+
+
+def _dense(t):
+    """t's values as they show, contiguous in memory."""
+    return t.resolve_conj().resolve_neg().contiguous()
+
+
+def _resolved(call, stream, ins, outs):
+    """call(ins, outs) with lazily conjugated or negated tensors of `ins`
+    resolved and those of `outs` replaced by new tensors that are copied back,
+    all on `stream`."""
+    def on_stream():
+        return contextlib.nullcontext() if stream is None else torch.cuda.stream(stream)
+    with torch.no_grad():
+        with on_stream():
+            ins = [_dense(t) if _is_lazy(t) else t for t in ins]
+            new = [torch.empty(t.shape, dtype=t.dtype, device=t.device) if _is_lazy(t) else t for t in outs]
+        result = call(ins, new)
+        with on_stream():
+            for t, n in zip(outs, new):
+                if t is not n:
+                    t.copy_(n)
+
+    def given(r):
+        return next((t for t, n in zip(outs, new) if n is r), r)
+    return tuple(given(r) for r in result) if isinstance(result, tuple) else given(result)
 
 
 def query(n: int, batch: int = 1, sign: int = -1, dtype: str = "c32") -> dict:
@@ -108,6 +142,8 @@ class Plan:
         return torch.empty(lead + (self.n // 2 + 1,), dtype=torch.complex64, device=x.device)
 
     def _run(self, fn, x, out, stream, to_spectrum):
+        if _is_lazy(x) or _is_lazy(out):
+            return _resolved(lambda i, o: self._run(fn, i[0], o[0], stream, to_spectrum), stream, [x], [out])
         if self.dtype == FFT_R32:
             sin, sout = self._sides(to_spectrum)
             self._check_tensor(x, "input", sin)
@@ -145,6 +181,8 @@ class Plan:
             r = calls().scaled(self._ref, x)
             if r is not NotImplemented:
                 return r
+        if _is_lazy(x) or _is_lazy(out):
+            return _resolved(lambda i, o: self.execute_scaled(i[0], in_exp, o[0], out_exp, stream), stream, [x], [out])
         self._check_tensor(x, "input")
         if out is None:
             out = torch.empty_like(x)
@@ -162,6 +200,8 @@ class Plan:
 
     def loss_grad(self, x, w, grad=None, loss=None, stream=None):
         """Fused loss[b] = sum_k w |(A x_b)_k|^2 and grad = A^H (2 w A x) (FP32 plans)."""
+        if any(_is_lazy(t) for t in (x, w, grad, loss)):
+            return _resolved(lambda i, o: self.loss_grad(i[0], i[1], o[0], o[1], stream), stream, [x, w], [grad, loss])
         self._check_tensor(x, "input")
         if w.dtype != torch.float32 or not w.is_cuda or not w.is_contiguous() or w.numel() != x.numel():
             raise ValueError("w must be a contiguous float32 GPU tensor shaped like x")
@@ -239,29 +279,29 @@ class RaggedPlan:
         if x.numel() != self.total:
             raise ValueError(f"{what} has {x.numel()} elements, plan needs {self.total}")
 
+    def _run(self, fn, x, out, stream):
+        if _is_lazy(x) or _is_lazy(out):
+            return _resolved(lambda i, o: self._run(fn, i[0], o[0], stream), stream, [x], [out])
+        self._check_tensor(x, "input")
+        if out is None:
+            out = torch.empty_like(x)
+        self._check_tensor(out, "output")
+        check(fn(self._h, _ptr(x), _ptr(out), _stream_handle(stream)))
+        return out
+
     def execute(self, x, out=None, stream=None):
         if stream is None:
             y = calls().run(self._ref, x, out, False)
             if y is not NotImplemented:
                 return y
-        self._check_tensor(x, "input")
-        if out is None:
-            out = torch.empty_like(x)
-        self._check_tensor(out, "output")
-        check(lib().fft_execute(self._h, _ptr(x), _ptr(out), _stream_handle(stream)))
-        return out
+        return self._run(lib().fft_execute, x, out, stream)
 
     def adjoint(self, g, out=None, stream=None):
         if stream is None:
             y = calls().run(self._ref, g, out, True)
             if y is not NotImplemented:
                 return y
-        self._check_tensor(g, "input")
-        if out is None:
-            out = torch.empty_like(g)
-        self._check_tensor(out, "output")
-        check(lib().fft_execute_adjoint(self._h, _ptr(g), _ptr(out), _stream_handle(stream)))
-        return out
+        return self._run(lib().fft_execute_adjoint, g, out, stream)
 
     def describe(self) -> dict:
         d = native.PlanDesc()
@@ -311,7 +351,7 @@ def fft(x, sign: int = -1):
     y = calls().call(_cache, x, sign, "c32", 0, 0, False)
     if y is not NotImplemented:
         return y
-    x = x.contiguous()
+    x = _dense(x)
     n = x.shape[-1]
     return get_plan(n, x.numel() // n, sign, "c32", x.device.index).execute(x)
 
@@ -329,7 +369,7 @@ class FFTFn(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, x, sign: int = -1):
-        x = x.contiguous()
+        x = _dense(x)
         n = x.shape[-1]
         plan = get_plan(n, x.numel() // n, sign, "c32", x.device.index)
         ctx.plan = plan
@@ -337,7 +377,7 @@ class FFTFn(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, grad_out):
-        g = grad_out.contiguous()
+        g = _dense(grad_out)
         if g.dtype != torch.complex64:
             g = g.to(torch.complex64)
         return ctx.plan.adjoint(g), None
@@ -362,8 +402,8 @@ class WeightedPowerLossFn(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, x, w, sign: int = -1):
-        x = x.contiguous()
-        w = w.contiguous()
+        x = _dense(x)
+        w = _dense(w)
         n = x.shape[-1]
         if n > FUSED_LOSS_MAX_N:
             raise ValueError(f"the fused loss kernel covers n <= {FUSED_LOSS_MAX_N} (got n={n}); "
@@ -393,7 +433,7 @@ def rfft(x):
     y = calls().call(_cache, x, -1, "r32", 0, 0, False)
     if y is not NotImplemented:
         return y
-    x = x.contiguous()
+    x = _dense(x)
     n = x.shape[-1]
     return get_plan(n, x.numel() // n, -1, "r32", x.device.index).execute(x)
 
@@ -405,7 +445,7 @@ def irfft(X, n: int | None = None):
     x = calls().call(_cache, X, +1, "r32", 0, n, False)
     if x is not NotImplemented:
         return x
-    X = X.contiguous()
+    X = _dense(X)
     if X.shape[-1] != n // 2 + 1:
         raise ValueError(f"{X.shape[-1]} bins given, n={n} needs {n // 2 + 1}")
     return get_plan(n, X.numel() // (n // 2 + 1), +1, "r32", X.device.index).execute(X)
@@ -417,14 +457,14 @@ class RFFTFn(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, x):
-        x = x.contiguous()
+        x = _dense(x)
         n = x.shape[-1]
         ctx.plan = get_plan(n, x.numel() // n, -1, "r32", x.device.index)
         return ctx.plan.execute(x)
 
     @staticmethod
     def backward(ctx, g):
-        g = g.contiguous()
+        g = _dense(g)
         if g.dtype != torch.complex64:
             g = g.to(torch.complex64)
         return ctx.plan.adjoint(g)
@@ -436,13 +476,13 @@ class IRFFTFn(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, X, n: int):
-        X = X.contiguous()
+        X = _dense(X)
         ctx.plan = get_plan(n, X.numel() // (n // 2 + 1), +1, "r32", X.device.index)
         return ctx.plan.execute(X)
 
     @staticmethod
     def backward(ctx, g):
-        g = g.contiguous()
+        g = _dense(g)
         if g.dtype != torch.float32:
             g = g.to(torch.float32)
         return ctx.plan.adjoint(g), None
@@ -498,7 +538,7 @@ def fftn(x, ndim: int | None = None, sign: int = -1):
     y = calls().call(_cache, x, sign, "nd", ndim, 0, False)
     if y is not NotImplemented:
         return y
-    x = x.contiguous()
+    x = _dense(x)
     shape = tuple(x.shape[x.dim() - ndim:])
     n = 1
     for d in shape:
@@ -523,7 +563,7 @@ class FFTNFn(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, x, ndim: int, sign: int = -1):
-        x = x.contiguous()
+        x = _dense(x)
         shape = tuple(x.shape[x.dim() - ndim:])
         n = 1
         for d in shape:
@@ -533,7 +573,7 @@ class FFTNFn(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, g):
-        g = g.contiguous()
+        g = _dense(g)
         if g.dtype != torch.complex64:
             g = g.to(torch.complex64)
         return ctx.plan.adjoint(g), None, None
