@@ -348,7 +348,7 @@ def get_plan(n: int, batch: int, sign: int, dtype: str = "c32", device=None) -> 
 
 def fft(x, sign: int = -1):
     """Transform over the last dimension of a complex64 GPU tensor (new tensor)."""
-    y = calls().call(_cache, x, sign, "c32", 0, 0, False)
+    y = calls().call(_cache, x, sign, "c32", 0, None, False)
     if y is not NotImplemented:
         return y
     x = _dense(x)
@@ -384,7 +384,7 @@ class FFTFn(torch.autograd.Function):
 
 
 def fft_differentiable(x, sign: int = -1):
-    y = calls().call(_cache, x, sign, "c32", 0, 0, True)
+    y = calls().call(_cache, x, sign, "c32", 0, None, True)
     if y is not NotImplemented:
         return y
     return FFTFn.apply(x, sign)
@@ -430,7 +430,7 @@ def weighted_power_loss(x, w, sign: int = -1):
 def rfft(x):
     """Bins 0..n/2 of the forward transform of a real float32 GPU tensor
     (last dimension n) as a new complex64 tensor (..., n/2 + 1)."""
-    y = calls().call(_cache, x, -1, "r32", 0, 0, False)
+    y = calls().call(_cache, x, -1, "r32", 0, None, False)
     if y is not NotImplemented:
         return y
     x = _dense(x)
@@ -489,7 +489,7 @@ class IRFFTFn(torch.autograd.Function):
 
 
 def rfft_differentiable(x):
-    y = calls().call(_cache, x, -1, "r32", 0, 0, True)
+    y = calls().call(_cache, x, -1, "r32", 0, None, True)
     if y is not NotImplemented:
         return y
     return RFFTFn.apply(x)
@@ -535,7 +535,7 @@ def fftn(x, ndim: int | None = None, sign: int = -1):
     """Transform over the last `ndim` dimensions (default all, at most 3) of
     a complex64 GPU tensor; new tensor."""
     ndim = x.dim() if ndim is None else int(ndim)
-    y = calls().call(_cache, x, sign, "nd", ndim, 0, False)
+    y = calls().call(_cache, x, sign, "nd", ndim, None, False)
     if y is not NotImplemented:
         return y
     x = _dense(x)
@@ -580,7 +580,7 @@ class FFTNFn(torch.autograd.Function):
 
 
 def fftn_differentiable(x, ndim: int, sign: int = -1):
-    y = calls().call(_cache, x, sign, "nd", ndim, 0, True)
+    y = calls().call(_cache, x, sign, "nd", ndim, None, True)
     if y is not NotImplemented:
         return y
     return FFTNFn.apply(x, ndim, sign)

@@ -291,9 +291,10 @@ PyObject* py_run(PyObject*, PyObject* const* a, Py_ssize_t n)
     });
 }
 
-// The cached plan for x: cache[(device, n, batch, sign, kind)], or for
-// `ndim` > 0 axes cache[(device, "nd", shape, batch, sign)].
-Plan* cached(PyObject* cache, const Tensor& x, int sign, PyObject* kind, int64_t ndim, int64_t n)
+// The cached plan for x: cache[(device, n, batch, sign, kind)], n the last
+// axis or, if `bins`, the length given for n / 2 + 1 bins; for `ndim` > 0 axes
+// cache[(device, "nd", shape, batch, sign)].
+Plan* cached(PyObject* cache, const Tensor& x, int sign, PyObject* kind, int64_t ndim, bool bins, int64_t n)
 {
     static PyObject* const nd = PyUnicode_InternFromString("nd");
     static PyObject* const attr = PyUnicode_InternFromString("_ref");
@@ -315,12 +316,10 @@ Plan* cached(PyObject* cache, const Tensor& x, int sign, PyObject* kind, int64_t
                          : Py_BuildValue("(iOOLi)", (int)x.get_device(), nd, shape, (long long)(x.numel() / points), sign);
         Py_DECREF(shape);
     } else {
-        // n reals of n / 2 + 1 bins, or the last axis itself
-        const int64_t per = n > 0 ? n / 2 + 1 : last;
-        if (per != last)
+        if (bins && (n < 2 || n / 2 + 1 != last))
             return nullptr;
-        key = Py_BuildValue("(iLLiO)", (int)x.get_device(), (long long)(n > 0 ? n : last),
-                            (long long)(x.numel() / per), sign, kind);
+        key = Py_BuildValue("(iLLiO)", (int)x.get_device(), (long long)(bins ? n : last),
+                            (long long)(x.numel() / last), sign, kind);
     }
     if (!key) {
         PyErr_Clear();
@@ -343,8 +342,9 @@ Plan* cached(PyObject* cache, const Tensor& x, int sign, PyObject* kind, int64_t
     return plan;
 }
 
-// call(cache, x, sign, kind, ndim, n, differentiable) -> tensor or
-// NotImplemented (no cached plan, or not the ordinary case)
+// call(cache, x, sign, kind, ndim, n or None, differentiable) -> tensor or
+// NotImplemented (no cached plan, or not the ordinary case); n: the length
+// that bins transform to
 PyObject* py_call(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     if (n != 7)
@@ -352,15 +352,16 @@ PyObject* py_call(PyObject*, PyObject* const* a, Py_ssize_t n)
     return guarded([&]() -> PyObject* {
         const Tensor* xp = plain_tensor(a[1]);
         if (!xp || !plain_context() || !PyLong_CheckExact(a[2]) || !PyLong_CheckExact(a[4]) ||
-            !PyLong_CheckExact(a[5]))
+            !(a[5] == Py_None || PyLong_CheckExact(a[5])))
             return not_implemented();
         const long sign = PyLong_AsLong(a[2]);
-        const long long ndim = PyLong_AsLongLong(a[4]), len = PyLong_AsLongLong(a[5]);
+        const bool bins = a[5] != Py_None;
+        const long long ndim = PyLong_AsLongLong(a[4]), len = bins ? PyLong_AsLongLong(a[5]) : 0;
         if (PyErr_Occurred()) {
             PyErr_Clear();
             return not_implemented();
         }
-        Plan* plan = cached(a[0], *xp, (int)sign, a[3], ndim, len);
+        Plan* plan = cached(a[0], *xp, (int)sign, a[3], ndim, bins, len);
         if (!plan || !side_ok(*xp, **plan, true, false) || !shape_ok(*xp, **plan, false))
             return not_implemented();
         const Plan keep = *plan;
@@ -390,7 +391,7 @@ PyObject* py_loss(PyObject*, PyObject* const* a, Py_ssize_t n)
             PyErr_Clear();
             return not_implemented();
         }
-        Plan* plan = cached(a[0], *xp, (int)sign, c32, 0, 0);
+        Plan* plan = cached(a[0], *xp, (int)sign, c32, 0, false, 0);
         if (!plan || (*plan)->n > 2048 || !side_ok(*xp, **plan, true, false))
             return not_implemented();
         if (!dense(*wp, at::kFloat) || wp->numel() != xp->numel())
