@@ -270,8 +270,10 @@ void load_tune_table()
     }
 }
 
-// bytes: of the call, per direction.
-Variant choose_c32(int log2n, int64_t bytes)
+// bytes: of the call, per direction.  last_axis: of a multidimensional plan,
+// in a pass of its own.  A measured table's entry holds for calls of every
+// size and in every place.
+Variant choose_c32(int log2n, int64_t bytes, bool last_axis = false)
 {
     std::call_once(g_tune_once, load_tune_table);
     if (g_have_tuned_c32[log2n]) {
@@ -279,7 +281,7 @@ Variant choose_c32(int log2n, int64_t bytes)
         if ((v.kind == 9 && log2n > 11) || find_c32(log2n, v.log2ept, v.wg, -1, v.kind))
             return v;
     }
-    return rule_or(kRulesC32, log2n, bytes, kDefaultC32[log2n]);
+    return rule_or(kRulesC32, log2n, bytes, last_axis && log2n == 11 ? kLastAxis2048 : kDefaultC32[log2n]);
 }
 
 Variant choose_loss(int log2n)
@@ -1099,14 +1101,9 @@ fft_plan create_nd(int rank, const int64_t* dims, int64_t batch, int sign, int d
     const bool tail2 = rank == 3 && find_nd2(ilog2(dims[1]), ilog2(dims[2]), sign) &&
                        find_nd2(ilog2(dims[1]), ilog2(dims[2]), -sign);
     const int64_t m = dims[rank - 1];
-    Variant v = choose_c32(ilog2(m), n * batch * 8);
-    const Variant &d = kDefaultC32[11], *force = nullptr;
-    if (m == 2048 && v.log2ept == d.log2ept && v.wg == d.wg && v.kind == d.kind) {
-        v = kLastAxis2048;
-        force = &v;
-    }
+    const Variant v = choose_c32(ilog2(m), n * batch * 8, true);
     mifft_plan_s* last = tail2 ? create_nd2(dims + 1, batch * dims[0], sign)
-                               : create_batched(m, batch * (n / m), sign, dtype, force);
+                               : create_batched(m, batch * (n / m), sign, dtype, &v);
     if (!last)
         return nullptr;
     auto* p = new (std::nothrow) mifft_plan_s();
