@@ -1320,9 +1320,7 @@ int exec_c32(fft_plan p, const void* in, void* out, int sign, float scale, hipSt
         return ok();
     }
     const KernelC32* k = sign < 0 ? p->fwd : p->bwd;
-    // (2^14 points, one workgroup per CU, are slower with plain stores)
-    const bool keep = k->feed && p->log2n < 14 && keep_output(p->total * (int64_t)sizeof(float2));
-    hipError_t e = (keep ? k->feed : k->fn)(in, out, p->tw, p->rows, p->batch, scale, p->grid_limit, st);
+    hipError_t e = k->fn(in, out, p->tw, p->rows, p->batch, scale, p->grid_limit, st);
     if (e != hipSuccess)
         return hip_err(e, "FFT kernel launch");
     return ok();

@@ -10,13 +10,14 @@
 //   next one reads its output, at the cache's rate: plain accesses.
 //   Measured with 16-column tile copies: 2 x 64 MiB, repeated on the same
 //   buffers, 17 us plain against 23 nontemporal; 2 x 512 MiB 205 against 189.
-// - Kept outputs.  One pass reads its input nontemporally at every size, but
-//   an output that fits the cache beside little else is stored plainly: the
-//   stores end in the cache while the reads use HBM, and the caller's next
-//   kernel finds them.  MI355X, three inputs and two outputs in turn,
-//   nontemporal -> plain stores: N = 64 at 128 MiB 42.6 -> 41.0 us, 256 MiB
-//   82.6 -> 78.6; N = 2048 at 96 MiB 35.7 -> 35.1, 256 MiB 90.1 -> 86.7;
-//   outside the range N = 2048 at 32 MiB 14.7 -> 15.5, 384 MiB 134.8 -> 144.1.
+// - One pass.  A transform of a single pass reads and stores nontemporally at
+//   every size.  Plain stores leave an output of up to 256 MiB in the cache,
+//   which helps a program that writes one buffer again and again or whose
+//   next kernel works on the output in place, and costs the others what
+//   the output drives out: N = 64 at 128 MiB, nontemporal -> plain stores, three
+//   inputs and one output in turn 0.96 of the time, in-place scaling after it
+//   0.94, three outputs 1.07, an input produced just before 1.03; at 250 MiB
+//   0.92, 0.86, 1.07 and 1.10.
 // - Chunks.  A transform of several passes over memory runs all its passes
 //   on one chunk of the batch before the next, so that a later pass reads
 //   what the earlier one left in the cache: the first pass reads its input
@@ -42,9 +43,6 @@ inline bool is_bulk(int64_t bytes) { return bytes > kBulkBytes; }
 
 // Whether a call that reads `bytes` and writes about as much is a stream.
 inline bool is_stream(int64_t bytes) { return bytes > kStreamBytes; }
-
-// Whether a pass that writes `bytes` stores them plainly.
-inline bool keep_output(int64_t bytes) { return bytes > (kStreamBytes >> 1) && bytes <= kChunkBytes; }
 
 // Units of `each` bytes in one chunk.
 inline int64_t chunk_units(int64_t each) { return each >= kChunkBytes ? 1 : kChunkBytes / each; }
