@@ -1265,16 +1265,19 @@ int exec_nd(fft_plan p, const void* in, void* out, int sign, hipStream_t st)
     // nontemporally, 314 -> 329).
     const int64_t cost = n * (int64_t)sizeof(float2) * (p->last->nd2_same ? 2 : 1);
     const int64_t outer = stream ? chunk_units(cost) : p->batch;
-    for (int64_t b = 0; b < p->batch; b += outer) {
-        const int64_t off = b * n, points = std::min(outer, p->batch - b) * n;
-        const int64_t step = stream && p->ax_first == 1 ? chunk_units(unit * (int64_t)sizeof(float2)) * unit : points;
-        for (int64_t u = 0; u < points; u += step) {
-            const int64_t here = std::min(step, points - u);
-            int rc = exec_last(p->last, src + off + u, dst + off + u, here / p->last->n, sign, st);
+    for (int64_t b = 0, arrays; b < p->batch; b += arrays) {
+        arrays = next_chunk(p->batch - b, outer, n * (int64_t)sizeof(float2));
+        const int64_t off = b * n, points = arrays * n;
+        const int64_t each = unit * (int64_t)sizeof(float2), units = points / unit;
+        const int64_t inner = stream && p->ax_first == 1 ? chunk_units(each) : units;
+        for (int64_t u = 0, take; u < units; u += take) {
+            take = next_chunk(units - u, inner, each);
+            const int64_t at = off + u * unit, here = take * unit;
+            int rc = exec_last(p->last, src + at, dst + at, here / p->last->n, sign, st);
             if (rc != FFT_OK)
                 return rc;
             if (p->ax_first == 1) {
-                const hipError_t e = axis(1, off + u, here);
+                const hipError_t e = axis(1, at, here);
                 if (e != hipSuccess)
                     return hip_err(e, "axis kernel launch");
             }

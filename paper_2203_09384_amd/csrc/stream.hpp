@@ -47,4 +47,18 @@ inline bool is_stream(int64_t bytes) { return bytes > kStreamBytes; }
 // Units of `each` bytes in one chunk.
 inline int64_t chunk_units(int64_t each) { return each >= kChunkBytes ? 1 : kChunkBytes / each; }
 
+// Units in the next chunk of a multidimensional transform with `left` to go,
+// `per` to a chunk: a last chunk of at most kTailBytes joins the one before it,
+// whose launches it shares, though the two then take a little more than the
+// cache (MI355X, us, whole batch plain -> short last chunk -> joined: 32^3 at
+// 136 MiB 109 -> 115 -> 107, at 150 MiB 119 -> 127 -> 115, 64^3 at 150 MiB
+// 115 -> 120 -> 111, 512 x 1024 at 280 MiB 238 -> 188 -> 184; but 44 MiB, 512 x 1024
+// at 300 MiB 254 -> 197 -> 205).  Chunks of equal size were slower than
+// either (32^3 at 136 MiB 121).
+constexpr int64_t kTailBytes = int64_t(32) << 20;
+inline int64_t next_chunk(int64_t left, int64_t per, int64_t each)
+{
+    return left > per && (left - per) * each > kTailBytes ? per : left;
+}
+
 }  // namespace mifft

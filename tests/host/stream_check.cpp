@@ -1,0 +1,13 @@
+// Host build of the rules on the sizes of calls
+// (paper_2203_09384_amd/csrc/stream.hpp) for the CPU tests.
+#include "stream.hpp"
+
+using namespace mifft;
+
+extern "C" {
+
+int64_t st_chunk_bytes() { return kChunkBytes; }
+int64_t st_tail_bytes() { return kTailBytes; }
+int64_t st_chunk_units(int64_t each) { return chunk_units(each); }
+int64_t st_next_chunk(int64_t left, int64_t per, int64_t each) { return next_chunk(left, per, each); }
+}

@@ -1,0 +1,56 @@
+"""CPU checks of the rules on the sizes of calls (csrc/stream.hpp): the chunks
+of a multidimensional transform cover its batch, none but the last exceeds a
+chunk, and no short one is left over."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2203_09384_amd", "csrc")
+I64 = ctypes.c_int64
+
+
+@pytest.fixture(scope="module")
+def st(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("st") / "libstream.so")
+    r = subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-fPIC", "-shared", f"-I{CSRC}",
+                        os.path.join(HERE, "host", "stream_check.cpp"), "-o", out], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    lib = ctypes.CDLL(out)
+    for f in ("st_chunk_bytes", "st_tail_bytes", "st_chunk_units", "st_next_chunk"):
+        getattr(lib, f).restype = I64
+    lib.st_chunk_units.argtypes = [I64]
+    lib.st_next_chunk.argtypes = [I64, I64, I64]
+    return lib
+
+
+def chunks(st, count, each, share):
+    """Sizes of the chunks of `count` units of `each` bytes; share: the bytes
+    of a chunk that a unit takes, in units of its own."""
+    per = st.st_chunk_units(share * each)
+    got, b = [], 0
+    while b < count:
+        here = st.st_next_chunk(count - b, per, each)
+        assert here >= 1
+        got.append(here)
+        b += here
+    assert b == count
+    return per, got
+
+
+@pytest.mark.parametrize("share", [1, 2])
+@pytest.mark.parametrize("log2_each", [15, 16, 20, 22, 23, 24, 25, 26, 28, 29])
+def test_chunks(st, share, log2_each):
+    each = 1 << log2_each
+    tail, whole = st.st_tail_bytes(), st.st_chunk_bytes() // share
+    per = st.st_chunk_units(share * each)
+    counts = {1, 2, 3, per, per + 1, 2 * per - 1, 2 * per, 2 * per + 1, 5 * per + 3}
+    counts |= {per + max(1, tail // each) + d for d in (-1, 0, 1)}
+    for count in sorted(c for c in counts if c >= 1):
+        per, got = chunks(st, count, each, share)
+        assert all(c == per for c in got[:-1])
+        assert got[-1] * each <= max(whole, each) + tail
+        if len(got) > 1 and got[-1] < per:
+            assert got[-1] * each > tail
