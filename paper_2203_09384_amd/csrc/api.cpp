@@ -1264,7 +1264,14 @@ int exec_nd(fft_plan p, const void* in, void* out, int sign, hipStream_t st)
     // 512 x 64 x 128 415 -> 391; 512 x 512, whose first pass reads
     // nontemporally, 314 -> 329).
     const int64_t cost = n * (int64_t)sizeof(float2) * (p->last->nd2_same ? 2 : 1);
-    const int64_t outer = stream ? chunk_units(cost) : p->batch;
+    // Volumes of 2 or 4 planes run as one chunk: the pass along so short an
+    // axis is far from the memory's rate, so it gains less from the cache than
+    // the launches cost (MI355X, us, whole batch plain -> 128 MiB chunks -> one
+    // chunk, last pass nontemporal: 2 x 128 x 128 at 500 MiB 643 -> 673 -> 640,
+    // 2 x 32 x 32 650 -> 681 -> 647, 4 x 128 x 128 482 -> 465 -> 448; but
+    // 8 x 64 x 64 414 -> 374 -> 393).
+    const bool few_planes = p->last->nd2_same && p->dims[0] <= 4;
+    const int64_t outer = stream && !few_planes ? chunk_units(cost) : p->batch;
     for (int64_t b = 0, arrays; b < p->batch; b += arrays) {
         arrays = next_chunk(p->batch - b, outer, n * (int64_t)sizeof(float2));
         const int64_t off = b * n, points = arrays * n;

@@ -43,3 +43,11 @@ def test_images(batch, sign):
 @pytest.mark.parametrize("batch", [513, 640, 641])
 def test_volumes(batch):
     check((32, 32, 32), batch, -1, [0, 511, 512, 513, batch - 1])
+
+
+# volumes of 2 and 4 planes, which run as one chunk, and of 8, which do not
+@pytest.mark.parametrize("shape,batch", [((2, 128, 128), 1100), ((4, 32, 32), 8200), ((8, 64, 64), 1050)], ids=str)
+@pytest.mark.parametrize("sign", [-1, 1])
+def test_few_planes(shape, batch, sign):
+    chunk = (128 << 17) // int(np.prod(shape))
+    check(shape, batch, sign, [0, chunk - 1, chunk, 2 * chunk - 1, 2 * chunk, batch - 1])
