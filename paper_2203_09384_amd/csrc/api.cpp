@@ -1222,8 +1222,8 @@ int exec_real(fft_plan p, const void* in, void* out, bool to_bins, float we, flo
 }
 
 // The sub-plan of a multidimensional plan (its last axis, or last two) over
-// `batch` of its transforms.
-int exec_last(fft_plan p, const void* in, void* out, int64_t batch, int sign, hipStream_t st)
+// `batch` of its transforms.  feeds: as LaunchFourStep.
+int exec_last(fft_plan p, const void* in, void* out, int64_t batch, int sign, bool feeds, hipStream_t st)
 {
     hipError_t e;
     if (p->nd2_same) {
@@ -1231,7 +1231,8 @@ int exec_last(fft_plan p, const void* in, void* out, int64_t batch, int sign, hi
         e = k->fn(in, out, p->nd2_rows[0], p->nd2_rows[1], batch, p->scale, st);
     } else if (p->fs) {
         e = (sign < 0 ? p->fs->fwd : p->fs->bwd)(in, out, p->fs_rows1, p->fs_rows2, p->fs_tw,
-                                                 static_cast<const float2*>(p->fs_tw) + 1024, batch, p->scale, st);
+                                                 static_cast<const float2*>(p->fs_tw) + 1024, batch, p->scale, feeds,
+                                                 st);
     } else {
         const KernelC32* k = sign < 0 ? p->fwd : p->bwd;
         e = (k->feed ? k->feed : k->fn)(in, out, p->tw, p->rows, batch, p->scale, p->grid_limit, st);
@@ -1272,6 +1273,10 @@ int exec_nd(fft_plan p, const void* in, void* out, int sign, hipStream_t st)
     // 8 x 64 x 64 414 -> 374 -> 393).
     const bool few_planes = p->last->nd2_same && p->dims[0] <= 4;
     const int64_t outer = stream && !few_planes ? chunk_units(cost) : p->batch;
+    // Where a four-step's output stays in the cache for the next pass; a pass
+    // along an axis of 2 does not gain (2 x 32768 at 400 MiB, nontemporal -> plain
+    // 627 -> 651 us, 4 x 32768 at 512 MiB 600 -> 578).
+    const bool feeds = stream && p->dims[0] > 2;
     for (int64_t b = 0, arrays; b < p->batch; b += arrays) {
         arrays = next_chunk(p->batch - b, outer, n * (int64_t)sizeof(float2));
         const int64_t off = b * n, points = arrays * n;
@@ -1280,7 +1285,8 @@ int exec_nd(fft_plan p, const void* in, void* out, int sign, hipStream_t st)
         for (int64_t u = 0, take; u < units; u += take) {
             take = next_chunk(units - u, inner, each);
             const int64_t at = off + u * unit, here = take * unit;
-            int rc = exec_last(p->last, src + at, dst + at, here / p->last->n, sign, st);
+            int rc = exec_last(p->last, src + at, dst + at, here / p->last->n, sign,
+                               feeds && take * each <= kChunkBytes + kTailBytes, st);
             if (rc != FFT_OK)
                 return rc;
             if (p->ax_first == 1) {
@@ -1324,7 +1330,7 @@ int exec_c32(fft_plan p, const void* in, void* out, int sign, float scale, hipSt
     if (p->fs) {
         const LaunchFourStep fn = sign < 0 ? p->fs->fwd : p->fs->bwd;
         hipError_t e = fn(in, out, p->fs_rows1, p->fs_rows2, p->fs_tw, static_cast<const float2*>(p->fs_tw) + 1024,
-                          p->batch, scale, st);
+                          p->batch, scale, false, st);
         if (e != hipSuccess)
             return hip_err(e, "four-step kernel launch");
         return ok();

@@ -5,9 +5,11 @@
 
 namespace mifft {
 
-// Launch both passes: in -> out (pass 1), out in place (pass 2).
+// Launch both passes: in -> out (pass 1), out in place (pass 2).  feeds: the
+// next kernel reads all of `out`, which fits the memory-side cache, so pass 2
+// leaves it there.
 using LaunchFourStep = hipError_t (*)(const void* in, void* out, const void* rows1, const void* rows2,
-                                      const void* tlo, const void* thi, int64_t batch, float scale,
+                                      const void* tlo, const void* thi, int64_t batch, float scale, bool feeds,
                                       hipStream_t stream);
 
 // Tables of a real-input plan above 2^15 (half length M = N1 N2, n = 2 M):

@@ -51,3 +51,13 @@ def test_volumes(batch):
 def test_few_planes(shape, batch, sign):
     chunk = (128 << 17) // int(np.prod(shape))
     check(shape, batch, sign, [0, chunk - 1, chunk, 2 * chunk - 1, 2 * chunk, batch - 1])
+
+
+# four-step last axes: one chunk, chunks with a joined and a separate tail,
+# three axes, an array beyond a chunk
+@pytest.mark.parametrize("shape,batch", [((32, 65536), 9), ((4, 32768), 258), ((4, 131072), 73), ((2, 8, 32768), 70),
+                                         ((2048, 32768), 1)], ids=str)
+@pytest.mark.parametrize("sign", [-1, 1])
+def test_four_step_last_axis(shape, batch, sign):
+    chunk = max(1, (256 << 17) // int(np.prod(shape)))
+    check(shape, batch, sign, [0, chunk - 1, chunk, batch - 1])
