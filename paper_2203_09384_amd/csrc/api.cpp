@@ -110,7 +110,7 @@ const FourStep* find_fourstep(int log2n, int64_t bytes)
 {
     const FourStep* found = nullptr;
     for (const auto& f : fs_reg())
-        if (f.log2n == log2n && (!f.bulk || is_bulk(bytes)) && (!found || f.bulk))
+        if (f.log2n == log2n && (!f.bulk || fourstep_bulk(log2n, bytes)) && (!found || f.bulk))
             found = &f;
     return found;
 }

@@ -44,6 +44,16 @@ inline bool is_bulk(int64_t bytes) { return bytes > kBulkBytes; }
 // Whether a call that reads `bytes` and writes about as much is a stream.
 inline bool is_stream(int64_t bytes) { return bytes > kStreamBytes; }
 
+// The same for the four-step passes (both of 2^15 and 2^16, the row pass of
+// 2^17).  2^15 between 64 MiB and a stream does not gain: MiB: us, three buffer
+// sets in turn, 72: 60.2 -> 62.5, 96: 76.1 -> 78.2, 128: 101.1 -> 104.1; two sets
+// 55.6 -> 58.0, 73.1 -> 76.5, 99.8 -> 103.1; one set 54.4 -> 48.6, 67.8 -> 65.5,
+// 88.7 -> 84.4; at 64 one or two sets 49.8 -> 44.1, three 53.1 -> 58.3.
+inline bool fourstep_bulk(int log2n, int64_t bytes)
+{
+    return is_bulk(bytes) && (log2n > 15 || bytes <= (kStreamBytes >> 1) || is_stream(bytes));
+}
+
 // Units of `each` bytes in one chunk.
 inline int64_t chunk_units(int64_t each) { return each >= kChunkBytes ? 1 : kChunkBytes / each; }
 

@@ -11,3 +11,10 @@ int64_t st_tail_bytes() { return kTailBytes; }
 int64_t st_chunk_units(int64_t each) { return chunk_units(each); }
 int64_t st_next_chunk(int64_t left, int64_t per, int64_t each) { return next_chunk(left, per, each); }
 }
+
+extern "C" {
+
+int64_t st_bulk_bytes() { return kBulkBytes; }
+int64_t st_stream_bytes() { return kStreamBytes; }
+int st_fourstep_bulk(int log2n, int64_t bytes) { return fourstep_bulk(log2n, bytes); }
+}

@@ -54,3 +54,16 @@ def test_chunks(st, share, log2_each):
         assert got[-1] * each <= max(whole, each) + tail
         if len(got) > 1 and got[-1] < per:
             assert got[-1] * each > tail
+
+
+@pytest.mark.parametrize("log2n", [15, 16, 17])
+def test_fourstep_bulk(st, log2n):
+    """32 points per thread: never in small calls, always in streams, and at
+    2^15 not between 64 MiB and a stream."""
+    for f in (st.st_bulk_bytes, st.st_stream_bytes):
+        f.restype = I64
+    st.st_fourstep_bulk.argtypes = [ctypes.c_int, I64]
+    bulk, stream = st.st_bulk_bytes(), st.st_stream_bytes()
+    for nbytes, want in ((0, False), (bulk, False), (bulk + 1, True), (stream // 2, True),
+                         (stream // 2 + 1, log2n != 15), (stream, log2n != 15), (stream + 1, True)):
+        assert bool(st.st_fourstep_bulk(log2n, nbytes)) == want, nbytes
