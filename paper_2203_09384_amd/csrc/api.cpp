@@ -1341,6 +1341,32 @@ int exec_c32(fft_plan p, const void* in, void* out, int sign, float scale, hipSt
         return hip_err(e, "FFT kernel launch");
     return ok();
 }
+
+int exec_loss_grad(fft_plan p, const void* x, const float* w, void* grad, float* loss, bool scaled_next, void* stream)
+{
+    int rc = check_exec(p, x, grad);
+    if (rc != FFT_OK)
+        return rc;
+    if (!w || !loss)
+        return set_err(FFT_ENULL, "w/loss pointer is NULL");
+    if (p->kind != 0 || p->dtype != FFT_C32 || !p->lossgrad)
+        return set_err(FFT_EINVAL_DTYPE, "the fused loss is provided for batched FFT_C32 plans of n <= 2048");
+    if ((reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(loss)) & 3)
+        return set_err(FFT_EALIGN, "w/loss must be 4-byte aligned");
+    const uintptr_t wb = reinterpret_cast<uintptr_t>(w), gb = reinterpret_cast<uintptr_t>(grad);
+    const uintptr_t wbytes = (uintptr_t)p->total * 4, gbytes = (uintptr_t)p->total * 8;
+    if (wb < gb + gbytes && gb < wb + wbytes)
+        return set_err(FFT_EOVERLAP, "w and grad overlap");
+    const uintptr_t lb = reinterpret_cast<uintptr_t>(loss), lbytes = (uintptr_t)p->batch * 4;
+    if (lb < gb + gbytes && gb < lb + lbytes)
+        return set_err(FFT_EOVERLAP, "loss and grad overlap");
+    const void* rows = p->lg_rows ? p->lg_rows : p->rows;
+    hipError_t e = p->lossgrad->fn(x, w, grad, loss, rows, p->batch, p->scale, p->lg_grid_limit, scaled_next,
+                                   static_cast<hipStream_t>(stream));
+    if (e != hipSuccess)
+        return hip_err(e, "fused loss kernel launch");
+    return ok();
+}
 }  // namespace
 
 // ------------------------------------------------------------------ C ABI
@@ -1582,28 +1608,13 @@ int fft_execute_scaled(fft_plan p, const void* in, const int32_t* in_exp, void* 
 
 int fft_execute_loss_grad(fft_plan p, const void* x, const float* w, void* grad, float* loss, void* stream)
 {
-    int rc = check_exec(p, x, grad);
-    if (rc != FFT_OK)
-        return rc;
-    if (!w || !loss)
-        return set_err(FFT_ENULL, "w/loss pointer is NULL");
-    if (p->kind != 0 || p->dtype != FFT_C32 || !p->lossgrad)
-        return set_err(FFT_EINVAL_DTYPE, "the fused loss is provided for batched FFT_C32 plans of n <= 2048");
-    if ((reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(loss)) & 3)
-        return set_err(FFT_EALIGN, "w/loss must be 4-byte aligned");
-    const uintptr_t wb = reinterpret_cast<uintptr_t>(w), gb = reinterpret_cast<uintptr_t>(grad);
-    const uintptr_t wbytes = (uintptr_t)p->total * 4, gbytes = (uintptr_t)p->total * 8;
-    if (wb < gb + gbytes && gb < wb + wbytes)
-        return set_err(FFT_EOVERLAP, "w and grad overlap");
-    const uintptr_t lb = reinterpret_cast<uintptr_t>(loss), lbytes = (uintptr_t)p->batch * 4;
-    if (lb < gb + gbytes && gb < lb + lbytes)
-        return set_err(FFT_EOVERLAP, "loss and grad overlap");
-    const void* rows = p->lg_rows ? p->lg_rows : p->rows;
-    hipError_t e = p->lossgrad->fn(x, w, grad, loss, rows, p->batch, p->scale, p->lg_grid_limit,
-                                   static_cast<hipStream_t>(stream));
-    if (e != hipSuccess)
-        return hip_err(e, "fused loss kernel launch");
-    return ok();
+    return exec_loss_grad(p, x, w, grad, loss, false, stream);
+}
+
+// For the binding's differentiable loss: the same, and the next kernel scales grad.
+int mifft_loss_grad_to_scale(fft_plan p, const void* x, const float* w, void* grad, float* loss, void* stream)
+{
+    return exec_loss_grad(p, x, w, grad, loss, true, stream);
 }
 
 void fft_plan_destroy(fft_plan p) { free_plan(p); }

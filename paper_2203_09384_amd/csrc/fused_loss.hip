@@ -166,10 +166,9 @@ __device__ __forceinline__ void loss_grad_group(cf (&v)[1 << E], cf (&nx)[1 << E
 }
 
 // PLAIN: the gradient stays in the memory-side cache, where the backward,
-// which scales it, finds it.  That pays while the whole gradient fits
-// (kChunkBytes): forward + backward at N = 2048, MI355X, nontemporal -> plain,
-// 256 MiB 216 -> 195 us, 128 MiB 113 -> 109, 512 MiB 422 -> 444.  Compiled
-// for the built-in shapes.
+// which scales it, finds it (keep_gradient says when that pays).  A call on its
+// own stores nontemporally: plain stores cost it 2-25 % (N = 64 at 250 MiB
+// 102 -> 125 us).  Compiled for the built-in shapes.
 //
 // Persistent: workgroups walk transform groups, loading the next group's x
 // while the current one is processed.
@@ -218,14 +217,14 @@ __global__ __launch_bounds__(WG) void k_fft_loss_grad(const cf* __restrict__ x, 
 
 template <int L, int E, int WG, int S>
 hipError_t launch_loss_grad(const void* x, const float* w, void* grad, float* loss, const void* rows,
-                            int64_t batch, float scale, int64_t grid_limit, hipStream_t stream)
+                            int64_t batch, float scale, int64_t grid_limit, bool scaled_next, hipStream_t stream)
 {
     constexpr int TPB = WG / Sched<L, E>::TPT;
     int64_t grid = (batch + TPB - 1) / TPB;
     if (grid_limit > 0 && grid > grid_limit)
         grid = grid_limit;
     constexpr bool builtin = kDefaultLoss[L].log2ept == E && kDefaultLoss[L].wg == WG;
-    const bool plain = builtin && batch * (int64_t(8) << L) <= kChunkBytes;
+    const bool plain = builtin && scaled_next && keep_gradient(L, batch * (int64_t(8) << L));
     return launch_kernel(plain ? k_fft_loss_grad<L, E, WG, S, builtin> : k_fft_loss_grad<L, E, WG, S, false>,
                          dim3((unsigned)grid), dim3(WG), 0, stream, static_cast<const cf*>(x), w,
                          static_cast<cf*>(grad), loss, static_cast<const cf*>(rows), batch, scale);

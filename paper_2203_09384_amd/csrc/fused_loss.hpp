@@ -8,9 +8,11 @@
 namespace mifft {
 
 // loss[b] = sum_k w |(A x_b)_k|^2 and grad_b = A^H (2 w A x_b) for the
-// batched FP32 transform A of sign `sign` and scale `scale`.
+// batched FP32 transform A of sign `sign` and scale `scale`.  scaled_next: the
+// next kernel scales grad (see keep_gradient).
 using LaunchLossGrad = hipError_t (*)(const void* x, const float* w, void* grad, float* loss, const void* rows,
-                                      int64_t batch, float scale, int64_t grid_limit, hipStream_t stream);
+                                      int64_t batch, float scale, int64_t grid_limit, bool scaled_next,
+                                      hipStream_t stream);
 
 // Fused loss-gradient kernel (two transforms per group, so its own best
 // shape differs from the plain transform's), per log2 N (index 1..11):

@@ -54,6 +54,19 @@ inline bool fourstep_bulk(int log2n, int64_t bytes)
     return is_bulk(bytes) && (log2n > 15 || bytes <= (kStreamBytes >> 1) || is_stream(bytes));
 }
 
+// Whether the differentiable loss stores its gradient of `bytes` plainly, so that
+// the backward, which scales it, finds it in a cache.  MI355X, forward +
+// backward in us, three inputs in turn, nontemporal -> plain: N = 2048 at 0.5 MiB
+// 8.0 -> 7.7, 2: 9.0 -> 8.8, 8: 15.2 -> 16.3, 24: 29.2 -> 29.8, 40: 39.9 -> 39.1,
+// 150: 127.5 -> 116.8, 250: 206 -> 184, 300: 244 -> 244; N = 128 at 0.5 MiB
+// 6.1 -> 5.8, 16: 18.4 -> 19.1, 40: 35.8 -> 33.7, 200: 148.5 -> 142.8,
+// 250: 186 -> 193.
+inline bool keep_gradient(int log2n, int64_t bytes)
+{
+    return bytes <= (kStreamBytes >> 6) ||
+           (bytes > (kStreamBytes >> 2) && bytes <= (log2n >= 9 ? kChunkBytes : kChunkBytes / 8 * 7));
+}
+
 // Units of `each` bytes in one chunk.
 inline int64_t chunk_units(int64_t each) { return each >= kChunkBytes ? 1 : kChunkBytes / each; }
 

@@ -36,6 +36,7 @@ struct Calls {
     int (*execute)(fft_plan, const void*, void*, void*) = nullptr;
     int (*adjoint)(fft_plan, const void*, void*, void*) = nullptr;
     int (*loss_grad)(fft_plan, const void*, const float*, void*, float*, void*) = nullptr;
+    int (*loss_grad_to_scale)(fft_plan, const void*, const float*, void*, float*, void*) = nullptr;
     int (*scaled)(fft_plan, const void*, const int32_t*, void*, int32_t*, void*) = nullptr;
     int (*scale)(const void*, const float*, void*, int64_t, void*) = nullptr;
     void (*destroy)(fft_plan) = nullptr;
@@ -180,13 +181,15 @@ struct LinearFn : torch::autograd::Function<LinearFn> {
 
 // L = sum_b sum_k w |(A x_b)_k|^2 with the gradient from the same kernel.
 struct LossFn : torch::autograd::Function<LossFn> {
-    static Tensor forward(torch::autograd::AutogradContext* ctx, const Tensor& x, const Tensor& w, const Plan& plan)
+    // to_scale: a backward will follow
+    static Tensor forward(torch::autograd::AutogradContext* ctx, const Tensor& x, const Tensor& w, const Plan& plan,
+                          bool to_scale)
     {
         Tensor grad = at::empty_like(x);
         Tensor loss = at::empty({plan->batch}, x.options().dtype(at::kFloat));
-        const int rc = g_calls.loss_grad(plan->h, x.data_ptr(), static_cast<const float*>(w.data_ptr()),
-                                         grad.data_ptr(), static_cast<float*>(loss.data_ptr()),
-                                         c10::hip::getCurrentHIPStream().stream());
+        const int rc = (to_scale ? g_calls.loss_grad_to_scale : g_calls.loss_grad)(
+            plan->h, x.data_ptr(), static_cast<const float*>(w.data_ptr()), grad.data_ptr(),
+            static_cast<float*>(loss.data_ptr()), c10::hip::getCurrentHIPStream().stream());
         if (rc != FFT_OK)
             raise_status(rc);
         ctx->save_for_backward({grad});
@@ -202,9 +205,9 @@ struct LossFn : torch::autograd::Function<LossFn> {
             Tensor out = at::empty_like(grad);
             if (g_calls.scale(grad.data_ptr(), static_cast<const float*>(g.data_ptr()), out.data_ptr(), grad.numel(),
                               c10::hip::getCurrentHIPStream().stream()) == 0)
-                return {out, Tensor(), Tensor()};
+                return {out, Tensor(), Tensor(), Tensor()};
         }
-        return {grad * g, Tensor(), Tensor()};
+        return {grad * g, Tensor(), Tensor(), Tensor()};
     }
 };
 
@@ -398,10 +401,11 @@ PyObject* py_loss(PyObject*, PyObject* const* a, Py_ssize_t n)
             return not_implemented();
         const Plan keep = *plan;
         const Tensor x = *xp, w = *wp;
+        const bool to_scale = at::GradMode::is_enabled() && x.requires_grad();
         Tensor out;
         {
             pybind11::gil_scoped_release nogil;
-            out = LossFn::apply(x, w, keep);
+            out = LossFn::apply(x, w, keep, to_scale);
         }
         return THPVariable_Wrap(std::move(out));
     });
@@ -434,16 +438,17 @@ PyObject* py_scaled(PyObject*, PyObject* const* a, Py_ssize_t n)
     });
 }
 
-// bind(execute, adjoint, loss_grad, scaled, scale, destroy, check)
+// bind(execute, adjoint, loss_grad, loss_grad_to_scale, scaled, scale, destroy, check)
 PyObject* py_bind(PyObject*, PyObject* args)
 {
-    unsigned long long e, d, l, s, c, x;
+    unsigned long long e, d, l, t, s, c, x;
     PyObject* check;
-    if (!PyArg_ParseTuple(args, "KKKKKKO", &e, &d, &l, &s, &c, &x, &check))
+    if (!PyArg_ParseTuple(args, "KKKKKKKO", &e, &d, &l, &t, &s, &c, &x, &check))
         return nullptr;
     g_calls.execute = reinterpret_cast<decltype(g_calls.execute)>(e);
     g_calls.adjoint = reinterpret_cast<decltype(g_calls.adjoint)>(d);
     g_calls.loss_grad = reinterpret_cast<decltype(g_calls.loss_grad)>(l);
+    g_calls.loss_grad_to_scale = reinterpret_cast<decltype(g_calls.loss_grad_to_scale)>(t);
     g_calls.scaled = reinterpret_cast<decltype(g_calls.scaled)>(s);
     g_calls.scale = reinterpret_cast<decltype(g_calls.scale)>(c);
     g_calls.destroy = reinterpret_cast<decltype(g_calls.destroy)>(x);

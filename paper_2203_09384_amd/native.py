@@ -132,8 +132,8 @@ def calls():
         m = importlib.util.module_from_spec(importlib.util.spec_from_loader("_mifft_torch", loader))
         loader.exec_module(m)
         m.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in
-                 (L.fft_execute, L.fft_execute_adjoint, L.fft_execute_loss_grad, L.fft_execute_scaled,
-                  L.mifft_scale_c32, L.fft_plan_destroy)), check)
+                 (L.fft_execute, L.fft_execute_adjoint, L.fft_execute_loss_grad, L.mifft_loss_grad_to_scale,
+                  L.fft_execute_scaled, L.mifft_scale_c32, L.fft_plan_destroy)), check)
         _calls = m
     return _calls
 

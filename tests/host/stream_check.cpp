@@ -18,3 +18,5 @@ int64_t st_bulk_bytes() { return kBulkBytes; }
 int64_t st_stream_bytes() { return kStreamBytes; }
 int st_fourstep_bulk(int log2n, int64_t bytes) { return fourstep_bulk(log2n, bytes); }
 }
+
+extern "C" int st_keep_gradient(int log2n, int64_t bytes) { return keep_gradient(log2n, bytes); }

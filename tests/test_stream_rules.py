@@ -67,3 +67,11 @@ def test_fourstep_bulk(st, log2n):
     for nbytes, want in ((0, False), (bulk, False), (bulk + 1, True), (stream // 2, True),
                          (stream // 2 + 1, log2n != 15), (stream, log2n != 15), (stream + 1, True)):
         assert bool(st.st_fourstep_bulk(log2n, nbytes)) == want, nbytes
+
+
+@pytest.mark.parametrize("log2n,most", [(1, 224), (8, 224), (9, 256), (11, 256)])
+def test_keep_gradient(st, log2n, most):
+    st.st_keep_gradient.argtypes = [ctypes.c_int, I64]
+    for nbytes, want in ((1 << 10, True), (2 << 20, True), ((2 << 20) + 8, False), (32 << 20, False), ((32 << 20) + 8, True), (most << 20, True),
+                         ((most << 20) + 8, False), (1 << 30, False)):
+        assert bool(st.st_keep_gradient(log2n, nbytes)) == want, nbytes
