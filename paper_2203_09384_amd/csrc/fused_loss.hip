@@ -60,6 +60,13 @@ __device__ __forceinline__ float transform_sum(float part)
     return part;
 }
 
+// Whether rows are read ahead of the exchange.  MI355X, us, after -> before:
+// 128 at 16 MiB 8.9 -> 8.7 (24: 11.3 -> 11.6), 256 at 24 MiB 12.2 -> 11.9, 1024 at
+// 64 MiB 39.7 -> 38.3, 2048 at 75 MiB 77.1 -> 76.1; 64 at 16 MiB 8.4 -> 8.6, 512 at
+// 16 MiB 9.4 -> 10.3.
+template <int L>
+constexpr bool kLossRowsAhead = L != 6 && L != 9;
+
 template <int L, int E, int S>
 __device__ __forceinline__ void transform_passes(cf (&v)[1 << E], int t, const cf* __restrict__ rows, cf* lds)
 {
@@ -73,7 +80,7 @@ __device__ __forceinline__ void transform_passes(cf (&v)[1 << E], int t, const c
     if constexpr (SC::TPT == 1)
         pass_compute2<L, E, S, 0>(v, tws[0]);
     else
-        run2<L, E, S, 1, (SC::TPT <= 64)>(v, t, rows, tws, lds);
+        run2<L, E, S, 1, (SC::TPT <= 64), 0, 0, kLossRowsAhead<L>>(v, t, rows, tws, lds);
 }
 
 // The forward passes of a group, loading the next group `gn` into `nx` a
