@@ -206,24 +206,30 @@ const Variant kDefaultR32[15] = {
     {4, 1024, 2},  // n=2^15
 };
 
-// Smaller calls (see kRulesC32 in registry.hpp for why).  MI355X, R2C + C2R
-// together in us, default -> rule, by MiB of reals:
+// Smaller calls (see kRulesC32 in registry.hpp for why), with limits of their own
+// where the directions differ: a plan's own direction counts, its adjoint runs
+// the same variant.  MI355X, R2C + C2R together or each in us, default -> rule,
+// by MiB of reals:
 //   n=32    16: 18.7 -> 16.8, 32: 29.6 -> 27.5 (48: 53.6 -> 57.9)
 //   n=64    16: 18.2 -> 15.9, 32: 31.1 -> 24.6 (64: 65.3 -> 63.7, 512: 439 -> 476)
-//   n=256   32: 29.5 -> 27.0, 64: 51.6 -> 48.1, 96: 84.2 -> 79.2 (128: 109 -> 109)
-//   n=512   0.5: 9.6 -> 6.6, 8: 12.1 -> 9.8, 16: 18.3 -> 16.6 (48: 41.9 -> 41.1)
+//   n=256   R2C 32: 18.9 -> 16.3, 64: 31.1 -> 26.7, 96: 43.4 -> 40.0 (128: 57 -> 57);
+//           C2R 24: 10.0 -> 9.9, 36: 14.0 -> 13.8 (64: 22.1 -> 23.4)
+//   n=512   0.5: 9.6 -> 6.6; R2C 8: 6.8 -> 5.9, 18: 12.2 -> 11.2 (24: 13.3 -> 13.7);
+//           C2R 8: 6.3 -> 5.1, 24: 11.5 -> 10.3 (R2C + C2R at 48: 41.9 -> 41.1)
 //   n=1024  0.5: 11.6 -> 6.8, 8: 13.5 -> 9.7, 32: 32.0 -> 28.0; 64: 56.0 -> 48.4,
 //           128: 109 -> 102 (512: 409 -> 416)
 //   n=2048  0.5: 8.0 -> 7.2, 16: 21.9 -> 18.0; 32: 35.3 -> 29.5, 64: 57.6 -> 51.3
 //           (128: 104 -> 104)
-//   n=2^12  0.5: 9.5 -> 7.7, 16: 22.5 -> 18.5, 32: 35.7 -> 31.3 (64: 55.8 -> 58.6)
+//   n=2^12  0.5: 9.5 -> 7.7, 16: 22.5 -> 18.5; R2C 28: 18.2 -> 17.1 (32: 19.1 -> 20.0);
+//           C2R 32: 18.2 -> 14.5 (R2C + C2R at 64: 55.8 -> 58.6)
 //   n=2^13  0.5: 13.4 -> 10.3, 16: 22.4 -> 19.9, 32: 36.4 -> 33.4 (64: 59.9 -> 62.1)
 // The defaults themselves at 512 MiB: n=2^13 with 16 points per thread 441,
 // with 8 411; n=2^14 persistent 652 us, one transform per workgroup 510.
 constexpr SizeRule kRulesR32[] = {
-    {4, 32, {2, 128, 7}},   {5, 32, {2, 256, 7}},  {7, 24, {3, 256, 6}},   {7, 96, {2, 256, 7}},
-    {8, 24, {3, 128, 6}},   {9, 32, {3, 64, 6}},   {9, 192, {3, 256, 7}},  {10, 24, {3, 128, 2}},
-    {10, 96, {3, 256, 3}},  {11, 32, {3, 256, 2}}, {12, 32, {3, 512, 2}},
+    {4, 32, {2, 128, 7}},      {5, 32, {2, 256, 7}},     {7, 24, {3, 256, 6}},     {7, 96, {2, 256, 7}, -1},
+    {7, 36, {2, 256, 7}, +1},  {8, 18, {3, 128, 6}, -1}, {8, 24, {3, 128, 6}, +1}, {9, 32, {3, 64, 6}},
+    {9, 192, {3, 256, 7}},     {10, 24, {3, 128, 2}},    {10, 96, {3, 256, 3}},    {11, 28, {3, 256, 2}, -1},
+    {11, 32, {3, 256, 2}, +1}, {12, 32, {3, 512, 2}},
 };
 
 std::once_flag g_tune_once;
@@ -281,7 +287,7 @@ Variant choose_c32(int log2n, int64_t bytes, bool last_axis = false)
         if ((v.kind == 9 && log2n > 11) || find_c32(log2n, v.log2ept, v.wg, -1, v.kind))
             return v;
     }
-    return rule_or(kRulesC32, log2n, bytes, last_axis && log2n == 11 ? kLastAxis2048 : kDefaultC32[log2n]);
+    return rule_or(kRulesC32, log2n, bytes, 0, last_axis && log2n == 11 ? kLastAxis2048 : kDefaultC32[log2n]);
 }
 
 Variant choose_loss(int log2n)
@@ -290,7 +296,7 @@ Variant choose_loss(int log2n)
     return g_have_tuned_loss[log2n] ? g_tuned_loss[log2n] : kDefaultLoss[log2n];
 }
 
-Variant choose_r32(int log2m, int64_t bytes)
+Variant choose_r32(int log2m, int64_t bytes, int sign)
 {
     std::call_once(g_tune_once, load_tune_table);
     if (g_have_tuned_r32[log2m]) {
@@ -298,7 +304,7 @@ Variant choose_r32(int log2m, int64_t bytes)
         if (find_real(log2m, v.log2ept, v.wg, 0, v.kind) && find_real(log2m, v.log2ept, v.wg, 1, v.kind))
             return v;
     }
-    return rule_or(kRulesR32, log2m, bytes, kDefaultR32[log2m]);
+    return rule_or(kRulesR32, log2m, bytes, sign, kDefaultR32[log2m]);
 }
 
 // Stockham schedule of (log2 N, log2 EPT): a remainder pass first, then
@@ -771,7 +777,7 @@ fft_plan create_real(int64_t n, int64_t batch, int sign, const Variant* force)
         return create_real_large(n, batch, sign);
     }
     const int log2m = ilog2(n) - 1;
-    const Variant v = force ? *force : choose_r32(log2m, n * batch * 4);
+    const Variant v = force ? *force : choose_r32(log2m, n * batch * 4, sign);
     const KernelReal* r2c = find_real(log2m, v.log2ept, v.wg, 0, v.kind);
     const KernelReal* c2r = find_real(log2m, v.log2ept, v.wg, 1, v.kind);
     if (!r2c || !c2r) {
@@ -1737,7 +1743,7 @@ int fft_plan_query(int64_t n, int64_t batch, int sign, int dtype, fft_plan_desc*
         return ok();
     }
     if (dtype == FFT_R32) {
-        const Variant v = choose_r32(ilog2(n) - 1, n * batch * 4);
+        const Variant v = choose_r32(ilog2(n) - 1, n * batch * 4, sign);
         if (!find_real(ilog2(n) - 1, v.log2ept, v.wg, sign < 0 ? 0 : 1, v.kind))
             return set_err(FFT_EINVAL_CONFIG, "no real-input kernel compiled for n=%lld", (long long)n);
         fill_desc_r32(n, batch, sign, v, 0, d);

@@ -48,8 +48,10 @@ constexpr Variant kDefaultC32[21] = {
 // than fill and drain their pipelines, and more, smaller threads per
 // transform finish sooner.  MI355X, us, default -> rule (three buffer sets
 // in turn):
-//   N=256   0.5 MiB 3.4 -> 2.9, 8 MiB 5.0 -> 4.5, 32 MiB 13.9 -> 13.4 (64: 24.1 -> 25.5)
-//   N=512   0.5 MiB 2.9 -> 2.7, 8 MiB 4.6 -> 4.2, 16 MiB 7.3 -> 6.7 (40: 15.9 -> 17.2)
+//   N=256   0.5 MiB 3.4 -> 2.9, 8 MiB 5.0 -> 4.5, 32 MiB 13.9 -> 13.4 (64: 24.1 -> 25.5);
+//           16 MiB 7.5 -> 8.4: the default's 1024 workgroups end there together,
+//           four to a CU (18 MiB 9.3 -> 9.1)
+//   N=512   0.5 MiB 2.9 -> 2.7, 8 MiB 5.1 -> 4.9, 15 MiB 7.8 -> 7.3 (16: 8.0 -> 8.5)
 //   N=1024  8 MiB 6.1 -> 4.8, 16 MiB 10.2 -> 7.0, 24 MiB 11.5 -> 9.6 (40: 17.1 -> 19.0);
 //           64 MiB 25.9 -> 24.8, 128 MiB 47.6 -> 46.4 (512: 182 -> 184)
 //   N=2048  8 MiB 5.3 -> 4.9, 16 MiB 8.7 -> 7.8, 24 MiB 12.0 -> 11.6 (32: 14.6 -> 15.2)
@@ -59,9 +61,10 @@ struct SizeRule {
     int log2;  // of the length (FFT_R32: of the half length)
     int mib;
     Variant v;
+    int sign = 0;  // of the plans it holds for; 0: both
 };
 constexpr SizeRule kRulesC32[] = {
-    {8, 32, {3, 64, 6}},   {9, 16, {3, 64, 6}},   {10, 24, {3, 128, 2}}, {10, 128, {3, 256, 3}},
+    {8, 14, {3, 64, 6}},   {8, 16, {4, 128, 12}}, {8, 32, {3, 64, 6}},   {9, 15, {3, 64, 6}},   {10, 24, {3, 128, 2}}, {10, 128, {3, 256, 3}},
     {11, 24, {3, 256, 2}}, {12, 16, {3, 512, 2}}, {13, 32, {4, 512, 2}},
 };
 
@@ -71,10 +74,10 @@ constexpr SizeRule kRulesC32[] = {
 constexpr Variant kLastAxis2048{4, 128, 3};
 
 template <size_t N>
-constexpr Variant rule_or(const SizeRule (&rules)[N], int log2, int64_t bytes, Variant otherwise)
+constexpr Variant rule_or(const SizeRule (&rules)[N], int log2, int64_t bytes, int sign, Variant otherwise)
 {
     for (const SizeRule& r : rules)
-        if (r.log2 == log2 && bytes <= (int64_t(r.mib) << 20))
+        if (r.log2 == log2 && (r.sign == 0 || r.sign == sign) && bytes <= (int64_t(r.mib) << 20))
             return r.v;
     return otherwise;
 }
