@@ -146,11 +146,12 @@ static std::vector<KernelAxis>& axis_reg()
     return r;
 }
 void register_axis(const KernelAxis& k) { axis_reg().push_back(k); }
-const KernelAxis* find_axis(int log2n, int sign, int64_t bytes)
+const KernelAxis* find_axis(int log2n, int sign, int64_t bytes, int64_t count, int log2s)
 {
     const KernelAxis* found = nullptr;
     for (const auto& k : axis_reg())
-        if (k.log2n == log2n && k.sign == sign && (!k.bulk || is_bulk(bytes)) && (!found || k.bulk))
+        if (k.log2n == log2n && k.sign == sign && (!k.bulk || is_bulk(bytes)) &&
+            (!k.narrow || axis_narrow(log2n, count, log2s)) && (!found || k.bulk || k.narrow))
             found = &k;
     return found;
 }
@@ -1041,6 +1042,18 @@ fft_plan create_nd3(const int64_t* dims, int64_t batch, int sign)
     return p;
 }
 
+// The kernel of axis `a` of `batch` arrays of `dims`.
+const KernelAxis* axis_kernel(const int64_t* dims, int rank, int a, int64_t batch, int sign)
+{
+    int64_t points = batch;
+    int log2s = 0;
+    for (int i = 0; i < rank; i++) {
+        points *= dims[i];
+        log2s += i > a ? ilog2(dims[i]) : 0;
+    }
+    return find_axis(ilog2(dims[a]), sign, points * (int64_t)sizeof(float2), points / dims[a], log2s);
+}
+
 fft_plan create_nd(int rank, const int64_t* dims, int64_t batch, int sign, int dtype)
 {
     if (!dims) {
@@ -1085,7 +1098,7 @@ fft_plan create_nd(int rank, const int64_t* dims, int64_t batch, int sign, int d
     if (rank == 1)
         return create_batched(dims[0], batch, sign, dtype, nullptr);
     for (int a = 0; a + 1 < rank; a++) {
-        const KernelAxis* k = find_axis(ilog2(dims[a]), sign, n * batch * (int64_t)sizeof(float2));
+        const KernelAxis* k = axis_kernel(dims, rank, a, batch, sign);
         if (!k) {
             set_err(FFT_EINVAL_CONFIG, "no axis kernel compiled for length %lld", (long long)dims[a]);
             return nullptr;
@@ -1139,8 +1152,8 @@ fft_plan create_nd(int rank, const int64_t* dims, int64_t batch, int sign, int d
     p->ax_first = tail2 ? 0 : rank - 2;
     for (int a = p->ax_first; a >= 0; a--) {
         const int L = ilog2(dims[a]);
-        p->ax_same[a] = find_axis(L, sign, p->total * (int64_t)sizeof(float2));
-        p->ax_opp[a] = find_axis(L, -sign, p->total * (int64_t)sizeof(float2));
+        p->ax_same[a] = axis_kernel(dims, rank, a, batch, sign);
+        p->ax_opp[a] = axis_kernel(dims, rank, a, batch, -sign);
         p->ax_log2s[a] = log2s;
         p->ax_scale[a] = sign > 0 ? 1.0f / (float)dims[a] : 1.0f;
         log2s += L;

@@ -71,6 +71,69 @@ hipError_t launch_axis(void* io, const void* rows, int64_t count, int log2s, flo
                   : launch_axis_nt<L, S, false, W>(p, r, count, log2s, scale, st);
 }
 
+// Tiles of 4 or 8 transforms, 16 points per thread, whole complex values in LDS
+// (71 KiB a tile of 4 at 2048 points: two workgroups per CU).  axis_narrow says
+// where they are the better split: a few transforms are bound by the length of
+// one workgroup's work, which this halves, and short strides by accesses of
+// less than a line, which 16 stores in flight bear better than 32.  Tiles that
+// share 128-byte lines run on one XCD.
+constexpr int NARROW_E = 4;
+
+template <int L, int S, int T>
+__global__ __launch_bounds__((T * ((1 << L) >> NARROW_E))) void k_axis_narrow(cf* __restrict__ io,
+                                                                         const cf* __restrict__ rows, int64_t count,
+                                                                         int log2s, float scale)
+{
+    constexpr int E = NARROW_E, EPT = 1 << E, TPT = (1 << L) >> E, ST = stage_stride<L, E>();
+    static_assert(TPT * T > 64, "exchanges span wavefronts");
+    __shared__ cf lds[T * ST];
+    const int tid = threadIdx.x, c = tid & (T - 1), t = tid / T;
+    const int64_t q0 = idx::xcd_group_tile(blockIdx.x, 16 / T) * T, q = q0 + c;
+    if (q0 >= count)
+        return;
+    const bool live = q < count;
+    cf* p = io + idx::axis_elem(live ? q : q0, t, L, log2s);
+    const int64_t step = (int64_t)TPT << log2s;
+    cf v[EPT];
+#pragma unroll
+    for (int m = 0; m < EPT; m++)
+        v[m] = ld_c(p + m * step);
+    TwRegs<L, E> tws;
+    unit_rows<L, E>(tws);
+    run2<L, E, S, 1, false, 0, 0, false>(v, t, rows, tws, lds + c * ST);
+    if (live) {
+#pragma unroll
+        for (int m = 0; m < EPT; m++)
+            st_c(p + m * step, cscale(v[m], scale));
+    }
+}
+
+template <int L, int S, int T>
+hipError_t launch_narrow_tiles(void* io, const void* rows, int64_t count, int log2s, float scale, hipStream_t st)
+{
+    constexpr int GROUP = 8 * (16 / T);  // whole groups for the XCD grouping
+    const int64_t tiles = (count + T - 1) / T;
+    return launch_kernel((k_axis_narrow<L, S, T>), dim3((unsigned)((tiles + GROUP - 1) / GROUP * GROUP)),
+                         dim3(T * ((1 << L) >> NARROW_E)), 0, st, static_cast<cf*>(io), static_cast<const cf*>(rows),
+                         count, log2s, scale);
+}
+
+template <int L, int S>
+hipError_t launch_axis_narrow(void* io, const void* rows, int64_t count, int log2s, float scale, bool, hipStream_t st)
+{
+    return narrow_tile(count, log2s) == 8 ? launch_narrow_tiles<L, S, 8>(io, rows, count, log2s, scale, st)
+                                          : launch_narrow_tiles<L, S, 4>(io, rows, count, log2s, scale, st);
+}
+
+template <int L>
+void add_axis_narrow()
+{
+    const int rows = Layout2<L, NARROW_E>::rows_total();
+    const int lds = 8 * stage_stride<L, NARROW_E>() * (int)sizeof(cf);
+    register_axis(KernelAxis{L, NARROW_E, -1, 4, &launch_axis_narrow<L, -1>, rows, lds, false, true});
+    register_axis(KernelAxis{L, NARROW_E, +1, 4, &launch_axis_narrow<L, +1>, rows, lds, false, true});
+}
+
 template <int L, bool W = false>
 void add_axis()
 {
@@ -81,8 +144,8 @@ void add_axis()
         lds = Wide<L>::PLANE * (int)sizeof(float);
     else
         lds = AXIS_TILE * stage_stride<L, E>() * (int)sizeof(cf);
-    register_axis(KernelAxis{L, E, -1, AXIS_TILE, &launch_axis<L, -1, W>, rows, lds, W});
-    register_axis(KernelAxis{L, E, +1, AXIS_TILE, &launch_axis<L, +1, W>, rows, lds, W});
+    register_axis(KernelAxis{L, E, -1, AXIS_TILE, &launch_axis<L, -1, W>, rows, lds, W, false});
+    register_axis(KernelAxis{L, E, +1, AXIS_TILE, &launch_axis<L, +1, W>, rows, lds, W, false});
 }
 
 struct AxisRegistrar {
@@ -101,6 +164,7 @@ struct AxisRegistrar {
         add_axis<9>();
         add_axis<10>();
         add_axis<11>();
+        add_axis_narrow<11>();
     }
 };
 AxisRegistrar axis_registrar;
