@@ -1254,7 +1254,8 @@ int exec_last(fft_plan p, const void* in, void* out, int64_t batch, int sign, bo
                                                  st);
     } else {
         const KernelC32* k = sign < 0 ? p->fwd : p->bwd;
-        e = (k->feed ? k->feed : k->fn)(in, out, p->tw, p->rows, batch, p->scale, p->grid_limit, st);
+        const bool plain = k->feed && feed_next(p->log2n, batch * p->n * (int64_t)sizeof(float2));
+        e = (plain ? k->feed : k->fn)(in, out, p->tw, p->rows, batch, p->scale, p->grid_limit, st);
     }
     return e == hipSuccess ? ok() : hip_err(e, "last-axis kernel launch");
 }
@@ -1262,8 +1263,8 @@ int exec_last(fft_plan p, const void* in, void* out, int64_t batch, int sign, bo
 // A multidimensional plan of several passes: the last axis (or two) from in
 // to out, then the other axes in place in `out`.  Streams run chunk by chunk
 // (stream.hpp) of whole arrays; where a 3D array alone exceeds a chunk, its
-// first two passes take chunks of planes.  The first pass stores plainly, the
-// last one reads and writes a stream nontemporally.  MI355X at 2^26 points,
+// first two passes take chunks of planes.  The first pass stores plainly
+// (feed_next), the last one reads and writes a stream nontemporally.  MI355X at 2^26 points,
 // before -> after: 2048 x 2048 441 -> 378 us, 1024 x 1024 385 -> 331,
 // 512 x 512 366 -> 319, 128^3 442 -> 407, 256^3 587 -> 483,
 // 16 x 1024 x 1024 620 -> 491; 1024 x 1024 x 16 111 -> 87.

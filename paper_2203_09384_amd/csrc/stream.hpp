@@ -67,6 +67,21 @@ inline bool keep_gradient(int log2n, int64_t bytes)
            (bytes > (kStreamBytes >> 2) && bytes <= (log2n >= 9 ? kChunkBytes : kChunkBytes / 8 * 7));
 }
 
+// Whether the first pass of a multidimensional transform, along 2^log2n points,
+// stores its `bytes` plainly for the next one.  Between 8 and 20 MiB it does not:
+// such an output lies in the XCDs' L2 caches (32 MiB together) and is written
+// back when the kernel ends, while nothing runs; smaller ones cost little, larger
+// ones leave on the way.  The window is a little wider at 128 and at 4096 points.
+// MI355X, us, nontemporal -> plain, one buffer set: 16 x 2048 at 1 MiB 6.8 -> 6.5,
+// 512 x 512 at 8 MiB 13.3 -> 12.9, 512 x 128 at 16 MiB 17.7 -> 20.2, 128 x 512 at
+// 24 MiB 25.9 -> 22.4, at 48 39.3 -> 34.0; 256 x 128 at 8 MiB 13.6 -> 14.1, 128 x
+// 4096 at 24 MiB 23.1 -> 24.9.
+inline bool feed_next(int log2n, int64_t bytes)
+{
+    constexpr int64_t MIB = int64_t(1) << 20;
+    return bytes <= (log2n == 7 ? 6 : 8) * MIB || bytes > (log2n == 12 ? 28 : 20) * MIB;
+}
+
 // Units of `each` bytes in one chunk.
 inline int64_t chunk_units(int64_t each) { return each >= kChunkBytes ? 1 : kChunkBytes / each; }
 

@@ -20,3 +20,5 @@ int st_fourstep_bulk(int log2n, int64_t bytes) { return fourstep_bulk(log2n, byt
 }
 
 extern "C" int st_keep_gradient(int log2n, int64_t bytes) { return keep_gradient(log2n, bytes); }
+
+extern "C" int st_feed_next(int log2n, int64_t bytes) { return feed_next(log2n, bytes); }

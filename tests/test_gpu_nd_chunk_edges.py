@@ -61,3 +61,14 @@ def test_few_planes(shape, batch, sign):
 def test_four_step_last_axis(shape, batch, sign):
     chunk = max(1, (256 << 17) // int(np.prod(shape)))
     check(shape, batch, sign, [0, chunk - 1, chunk, batch - 1])
+
+
+# sizes at which the first pass's stores change, and one array above
+@pytest.mark.parametrize("shape,low,high", [((1024, 32), 8, 20), ((256, 128), 6, 20), ((128, 256), 8, 20),
+                                            ((64, 512), 8, 20), ((32, 1024), 8, 20), ((16, 2048), 8, 20),
+                                            ((8, 4096), 8, 28), ((4, 16384), 8, 20)], ids=str)
+def test_first_pass_stores(shape, low, high):
+    n = int(np.prod(shape))
+    for mib in (low, high):
+        for batch in ((mib << 17) // n, (mib << 17) // n + 1):
+            check(shape, batch, -1, [0, batch // 2, batch - 1])

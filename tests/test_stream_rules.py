@@ -75,3 +75,11 @@ def test_keep_gradient(st, log2n, most):
     for nbytes, want in ((1 << 10, True), (2 << 20, True), ((2 << 20) + 8, False), (32 << 20, False), ((32 << 20) + 8, True), (most << 20, True),
                          ((most << 20) + 8, False), (1 << 30, False)):
         assert bool(st.st_keep_gradient(log2n, nbytes)) == want, nbytes
+
+
+@pytest.mark.parametrize("log2n,low,high", [(1, 8, 20), (7, 6, 20), (8, 8, 20), (12, 8, 28), (14, 8, 20)])
+def test_feed_next(st, log2n, low, high):
+    st.st_feed_next.argtypes = [ctypes.c_int, I64]
+    for mib, extra, want in ((0, 8, True), (low, 0, True), (low, 8, False), (16, 0, False), (high, 0, False),
+                             (high, 8, True), (256, 0, True)):
+        assert bool(st.st_feed_next(log2n, (mib << 20) + extra)) == want, (mib, extra)
