@@ -306,8 +306,17 @@ __device__ __forceinline__ cf unsplit_bin(cf a, cf b, cf w)
 // through LDS, one float plane at a time.  All tiles of a transform run on
 // one XCD while there are 8 transforms to deal (bins rows start at odd
 // multiples of 8 bytes, so tiles share lines, which meet in that XCD's L2).
+//
+// Narrow tiles (T = 16) of up to 128 threads run where there are few of them:
+// registers are not limited for four wavefronts per SIMD, so that all of a
+// thread's loads are in flight.  MI355X, R2C in us, limited -> not: n = 2^16 x 2
+// 12.1 -> 11.8, 2^17 x 1 13.0 -> 12.4, x 48 29.1 -> 27.5, 2^18 x 6 22.2 -> 20.7 (256 threads,
+// 2^19 x 2 19.6 -> 19.9).
+template <int L2, int T>
+constexpr int split_waves() { return T == 16 && Wide<L2, T>::WG <= 128 ? 1 : WIDE_WAVES; }
+
 template <int L1, int L2, int T>
-__global__ __launch_bounds__((Wide<L2, T>::WG), WIDE_WAVES) void k_rows_split(
+__global__ __launch_bounds__((Wide<L2, T>::WG), (split_waves<L2, T>())) void k_rows_split(
     const cf* __restrict__ ws, cf* __restrict__ out, const cf* __restrict__ rows, const cf* __restrict__ rlo,
     const cf* __restrict__ rhi, int64_t batch, float we, float wi)
 {
