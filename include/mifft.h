@@ -86,7 +86,11 @@ enum {
     FFT_ECAPTURE = 13       /* plan creation while a stream capture is active   */
 };
 
-/* Description of what a plan launches (fft_plan_describe / fft_plan_query). */
+/* Description of what a plan launches (fft_plan_describe / fft_plan_query).
+ * Four-step transforms (variant 9, and FFT_R32 above 2^15, whose passes hold the
+ * even/odd split): ept, wg, transforms_per_wg (columns) and grid are the first
+ * pass's, grid over all its launches; radices are both passes', lds_bytes the
+ * larger of the two. */
 typedef struct {
     int64_t n;          /* transform length (batched plans), 0 for ragged     */
     int64_t batch;      /* transforms per execute                             */
@@ -94,7 +98,7 @@ typedef struct {
     int dtype;          /* FFT_C32 / FFT_C16 / FFT_CBF16 / FFT_R32             */
     float scale;        /* output scale: 1 (forward) or 1/n (inverse)         */
     int ept;            /* complex elements held per thread (FFT_R32: of the
-                           half-length transform, as npasses and radices)  */
+                           half-length transform, as npasses and radices)   */
     int wg;             /* threads per workgroup                              */
     int transforms_per_wg;
     int64_t grid;       /* workgroups per execute (persistent kernels: those

@@ -376,7 +376,7 @@ struct mifft_plan_s {
 namespace {
 constexpr int64_t kMaxN = int64_t(1) << 20;
 constexpr int64_t kMaxRealN = int64_t(1) << 21;
-constexpr int64_t kMaxFusedRealN = int64_t(1) << 15;  // above: four-step half length + split pass
+constexpr int64_t kMaxFusedRealN = int64_t(1) << 15;  // above: four-step half length, the split in its passes
 
 int check_common(int64_t n, int64_t batch, int sign, int dtype)
 {
@@ -399,7 +399,9 @@ int check_common(int64_t n, int64_t batch, int sign, int dtype)
     return FFT_OK;
 }
 
-int fill_desc_fourstep(int64_t n, int64_t batch, int sign, int dtype, fft_plan_desc* d)
+// real: 0 for a complex transform of n points, else the sign of a real-input
+// one of 2 n, whose passes hold the split.
+int fill_desc_fourstep(int64_t n, int64_t batch, int sign, int dtype, int real, fft_plan_desc* d)
 {
     memset(d, 0, sizeof *d);
     const FourStep* f = find_fourstep(ilog2(n), n * batch * (int64_t)sizeof(float2));
@@ -412,23 +414,25 @@ int fill_desc_fourstep(int64_t n, int64_t batch, int sign, int dtype, fft_plan_d
     d->variant = 9;
     if (!f)
         return FFT_OK;
-    d->ept = 1 << f->log2e1;
-    d->wg = f->tile1 * (int)((1 << f->log2n1) >> f->log2e1);
-    d->transforms_per_wg = f->tile1;
-    d->grid = batch * ((int64_t(1) << f->log2n2) / f->tile1);
+    const PassShape cols = f->pass(real > 0 ? kFsUnsplitCols : kFsCols, batch);
+    const PassShape rows = f->pass(real < 0 ? kFsSplitRows : kFsRows, batch);
+    d->ept = 1 << cols.log2e;
+    d->wg = cols.wg;
+    d->transforms_per_wg = cols.tile;
+    d->grid = batch * ((int64_t(1) << f->log2n2) / cols.tile);
     int r1[8], r2[8];
-    const int n1 = schedule(f->log2n1, f->log2e1, r1), n2 = schedule(f->log2n2, f->log2e2, r2);
+    const int n1 = schedule(f->log2n1, cols.log2e, r1), n2 = schedule(f->log2n2, rows.log2e, r2);
     d->npasses = std::min(8, n1 + n2);
     for (int i = 0; i < d->npasses; i++)
         d->radices[i] = i < n1 ? r1[i] : r2[i - n1];
-    d->lds_bytes = std::max(f->lds1, f->lds2);
+    d->lds_bytes = std::max(cols.lds, rows.lds);
     return FFT_OK;
 }
 
 int fill_desc_c32(int64_t n, int64_t batch, int sign, int dtype, Variant v, int64_t grid_limit, fft_plan_desc* d)
 {
     if (v.kind == 9)
-        return fill_desc_fourstep(n, batch, sign, dtype, d);
+        return fill_desc_fourstep(n, batch, sign, dtype, 0, d);
     memset(d, 0, sizeof *d);
     const int log2n = ilog2(n);
     d->n = n;
@@ -456,8 +460,8 @@ int fill_desc_c32(int64_t n, int64_t batch, int sign, int dtype, Variant v, int6
 int fill_desc_r32(int64_t n, int64_t batch, int sign, Variant v, int64_t grid_limit, fft_plan_desc* d)
 {
     if (n > kMaxFusedRealN) {
-        // the half-length four-step transform (plus the split pass)
-        fill_desc_fourstep(n / 2, batch, sign, FFT_C32, d);
+        // the half-length four-step transform with the split in its passes
+        fill_desc_fourstep(n / 2, batch, sign, FFT_C32, sign, d);
         d->n = n;
         d->dtype = FFT_R32;
         d->scale = sign > 0 ? 1.0f / (float)n : 1.0f;
@@ -706,11 +710,6 @@ fft_plan create_batched(int64_t n, int64_t batch, int sign, int dtype, const Var
 fft_plan create_real_large(int64_t n, int64_t batch, int sign)
 {
     const int64_t m = n / 2;
-    const int64_t kblocks = ((m / 2 + 1) + 255) / 256;
-    if (batch > 0x7fffffffLL / kblocks) {
-        set_err(FFT_EINVAL_BATCH, "batch=%lld needs more than 2^31-1 workgroups", (long long)batch);
-        return nullptr;
-    }
     mifft_plan_s* sub = create_batched(m, batch, sign, FFT_C32, nullptr);
     if (!sub)
         return nullptr;

@@ -596,16 +596,44 @@ hipError_t launch_c2r(const void* in, void* out, const RealTables& t, int64_t ba
     return hipSuccess;
 }
 
-// log2 of the points per thread, and the LDS bytes, of an inner transform.
+// log2 of the points per thread of an inner transform, and the bytes of the
+// column pass's twiddle tables in LDS.
 constexpr int fs_e(int Li, bool W) { return wide_len(Li, W) ? WIDE_E : inner_e(Li); }
 
+constexpr int fs_tw(int L) { return tw3_in_lds(L) ? (64 + (1 << (L - 10))) * (int)sizeof(cf) : (int)sizeof(cf); }
+
+// Pass shapes as the launches above choose them: an inner transform of 2^Li in
+// tiles of 8 where narrow_tiles(count) and not NT, else of 16.
 template <int Li, bool W>
-constexpr int fs_lds()
+PassShape inner_shape(bool nt, int64_t count, bool cols, int tw)
 {
-    if constexpr (wide_len(Li, W))
-        return Wide<Li>::PLANE * (int)sizeof(float);
-    else
-        return TILE * stage_stride<Li, inner_e(Li)>() * (int)sizeof(cf);
+    if constexpr (wide_len(Li, W)) {
+        const bool narrow = !nt && narrow_tiles(count);
+        const int plane = cols ? (narrow ? col_plane<Li, 8>() : col_plane<Li, 16>())
+                               : (narrow ? Wide<Li, 8>::PLANE : Wide<Li, 16>::PLANE);
+        return PassShape{WIDE_E, narrow ? 8 : 16, narrow ? Wide<Li, 8>::WG : Wide<Li, 16>::WG, plane * (int)sizeof(float) + tw};
+    } else {
+        constexpr int E = inner_e(Li);
+        return PassShape{E, TILE, TILE * ((1 << Li) >> E), TILE * stage_stride<Li, E>() * (int)sizeof(cf) + tw};
+    }
+}
+
+template <int L1, int L2, bool W>
+PassShape pass_shape(FsPass pass, int64_t batch)
+{
+    constexpr int64_t M = int64_t(1) << (L1 + L2);
+    const bool nt = is_stream(batch * M * (int64_t)sizeof(cf));
+    const int64_t chunk = fs_ws_transforms(M, batch);  // of real input
+    switch (pass) {
+    case kFsCols: return inner_shape<L1, W>(nt, batch << L2, true, fs_tw(L1 + L2));
+    case kFsRows: return inner_shape<L2, W>(nt, batch << L1, false, 0);
+    case kFsSplitRows: {
+        const bool narrow = narrow_tiles(chunk << (L1 - 1));
+        return narrow ? PassShape{WIDE_E, 16, Wide<L2, 16>::WG, (Wide<L2, 16>::PLANE + 16) * (int)sizeof(float)}
+                      : PassShape{WIDE_E, 32, Wide<L2, 32>::WG, (Wide<L2, 32>::PLANE + 32) * (int)sizeof(float)};
+    }
+    default: return inner_shape<L1, true>(false, chunk << L2, true, fs_tw(L1 + L2));
+    }
 }
 
 struct RealFns {
@@ -628,10 +656,9 @@ void add_len()
 {
     constexpr int L1 = (L + 1) / 2, L2 = L / 2;
     constexpr int E1 = fs_e(L1, W), E2 = fs_e(L2, W);
-    const int tw = tw3_in_lds(L) ? (64 + (1 << (L - 10))) * (int)sizeof(cf) : 0;
     const FourStep fs{L, L1, L2, E1, E2, Layout2<L1, E1>::rows_total(), Layout2<L2, E2>::rows_total(),
-                      &launch_fourstep<L1, L2, -1, W>, &launch_fourstep<L1, L2, +1, W>, fs_lds<L1, W>() + tw,
-                      fs_lds<L2, W>(), TILE, real_fns<L1, L2, W>().r2c, real_fns<L1, L2, W>().c2r, W};
+                      &launch_fourstep<L1, L2, -1, W>, &launch_fourstep<L1, L2, +1, W>, &pass_shape<L1, L2, W>,
+                      real_fns<L1, L2, W>().r2c, real_fns<L1, L2, W>().c2r, W};
     register_fourstep(fs);
 }
 

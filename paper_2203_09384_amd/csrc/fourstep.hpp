@@ -27,13 +27,22 @@ using LaunchFsR2C = hipError_t (*)(const void* in, void* out, void* ws, const Re
 using LaunchFsC2R = hipError_t (*)(const void* in, void* out, const RealTables& t, int64_t batch, float we, float wi,
                                    hipStream_t stream);
 
+// One pass's workgroups: points per thread (log2), transforms, threads and LDS
+// bytes of each.
+struct PassShape {
+    int log2e, tile, wg, lds;
+};
+// The passes of a call of `batch` transforms: the complex column and row pass,
+// R2C's row pass with the split, C2R's column pass with the reverse split.
+enum FsPass { kFsCols, kFsRows, kFsSplitRows, kFsUnsplitCols };
+using FsPassShape = PassShape (*)(FsPass pass, int64_t batch);
+
 struct FourStep {
     int log2n, log2n1, log2n2;  // N = N1 * N2, column length N1, row length N2
     int log2e1, log2e2;         // elements per thread of the inner transforms
     int rows1, rows2;           // twiddle-row entries of the inner transforms
     LaunchFourStep fwd, bwd;    // sign -1 / +1
-    int lds1, lds2;             // LDS per workgroup of each pass
-    int tile1;                  // columns per pass-1 workgroup
+    FsPassShape pass;
     LaunchFsR2C r2c;            // real input of twice the length (M >= 2^15)
     LaunchFsC2R c2r;
     bool bulk;                  // for calls that fill the chip (is_bulk)
