@@ -288,7 +288,8 @@ Variant choose_c32(int log2n, int64_t bytes, bool last_axis = false)
         if ((v.kind == 9 && log2n > 11) || find_c32(log2n, v.log2ept, v.wg, -1, v.kind))
             return v;
     }
-    return rule_or(kRulesC32, log2n, bytes, 0, last_axis && log2n == 11 ? kLastAxis2048 : kDefaultC32[log2n]);
+    const bool l16 = last_axis && log2n == 11 && is_stream(bytes);
+    return rule_or(kRulesC32, log2n, bytes, 0, l16 ? kLastAxis2048 : kDefaultC32[log2n]);
 }
 
 Variant choose_loss(int log2n)

@@ -112,8 +112,8 @@ __global__ __launch_bounds__(WG) void k_fft_c32(const cf* __restrict__ in, cf* _
 // byte offset; LDS addresses are one per-thread base plus immediates.
 
 // Whether rows are read ahead of the exchange.  MI355X, us, after -> before:
-//   512 at 12 MiB 5.26 -> 5.05, 2^12 at 15 MiB 7.49 -> 7.14, 2^14 at 12 MiB
-//   15.1 -> 14.0, at 80 MiB 51.0 -> 48.7;
+//   256 at 10 MiB 5.9 -> 5.5 (28: 12.8 -> 13.0), 512 at 12 MiB 5.26 -> 5.05, 2^12
+//   at 15 MiB 7.49 -> 7.14, 2^14 at 12 MiB 15.1 -> 14.0, at 80 MiB 51.0 -> 48.7;
 //   1024 at 24 MiB 9.7 -> 11.7, 2048 at 22 MiB 11.3 -> 12.0, 2^13 at 30 MiB
 //   15.9 -> 17.0.
 template <int L>
@@ -403,7 +403,7 @@ constexpr bool is_last_axis(int L, int E, int WG, int kind)
     for (const SizeRule& r : kRulesC32)
         if (r.log2 == L && same(r.v))
             return true;
-    return same(L == 11 ? kLastAxis2048 : kDefaultC32[L]);
+    return same(kDefaultC32[L]) || (L == 11 && same(kLastAxis2048));
 }
 
 // Variant menu, v1: EPT in {2,4,8,16} (not above N; at least 4 once

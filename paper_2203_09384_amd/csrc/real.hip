@@ -81,7 +81,8 @@ __device__ __forceinline__ void load_bins(cf (&a)[1 << E], cf& aM, const cf* __r
 
 // Whether rows are read ahead of the exchange (SIGN -1: R2C).  MI355X, us,
 // after -> before:
-//   n = 2^13 at 24 MiB 14.4 -> 14.2, 2^15 at 60 MiB 45.5 -> 42.8 (C2R 45.5 ->
+//   n = 2^12 at 4 MiB 5.1 -> 4.9, at 16 11.3 -> 10.9 (C2R 4.9 -> 4.7, 8.5 -> 8.5; from
+//   40 equal), 2^13 at 24 MiB 14.4 -> 14.2, 2^15 at 60 MiB 45.5 -> 42.8 (C2R 45.5 ->
 //   42.1), C2R 2^14 at 60 MiB 32.1 -> 31.1;
 //   32 at 200 MiB 93.8 -> 101.4, 128 at 200 MiB 85.3 -> 87.7, 256 at 24 MiB
 //   13.1 -> 13.3, C2R 2048 at 24 MiB 9.8 -> 10.0, R2C 2^14 at 60 MiB 36.4 ->

@@ -64,13 +64,16 @@ struct SizeRule {
     int sign = 0;  // of the plans it holds for; 0: both
 };
 constexpr SizeRule kRulesC32[] = {
-    {8, 14, {3, 64, 6}},   {8, 16, {4, 128, 12}}, {8, 32, {3, 64, 6}},   {9, 15, {3, 64, 6}},   {10, 24, {3, 128, 2}}, {10, 128, {3, 256, 3}},
-    {11, 24, {3, 256, 2}}, {12, 16, {3, 512, 2}}, {13, 32, {4, 512, 2}},
+    {8, 14, {3, 64, 6}},    {8, 16, {4, 128, 12}}, {8, 32, {3, 64, 6}},  {9, 15, {3, 64, 6}},  {10, 24, {3, 128, 2}},
+    {10, 128, {3, 256, 3}}, {11, 24, {3, 256, 2}}, {12, 16, {3, 512, 2}}, {13, 32, {4, 512, 2}},
 };
 
 // The last axis of a multidimensional plan, storing plainly for the next
-// pass, keeps 16 points per thread at 2048 points (2D 2048 x 2048 x 16, 16
-// against 8 points: 374 against 380 us; plain calls 183.4 against 181.2).
+// pass, keeps 16 points per thread at 2048 points in streams (is_stream).
+// MI355X, us, 16 -> 8 points: 2048 x 2048 x 8 191 -> 196, x 16 375 -> 378, 1024 x
+// 2048 x 16 166 -> 166, 8 x 2048 x 1600 126 -> 127 (2 x 2048, 16 x 2048 and
+// 256 x 2048 differ by at most 2 % either way); below a stream 8 x 2048 x 320
+// 35.4 -> 34.0, 64 x 2048 x 64 48.7 -> 46.5, 2048 x 2048 x 2 53.1 -> 51.0.
 constexpr Variant kLastAxis2048{4, 128, 3};
 
 template <size_t N>
@@ -91,9 +94,9 @@ struct KernelC32 {
     int (*occupancy)();       // workgroups per CU (persistent kinds), else NULL
     int rows;                 // twiddle-row entries the variant needs (kind >= 1)
     int lds_bytes;            // LDS per workgroup
-    // the same with plain stores, which stay in the memory-side cache for the
-    // next pass of a multidimensional transform; compiled for the
-    // variants that those run, else NULL
+    // the same with plain stores, which stay in the caches for the next pass of
+    // a multidimensional transform (plain calls store nontemporally); compiled
+    // for the variants that those run, else NULL
     LaunchC32 feed;
 };
 
