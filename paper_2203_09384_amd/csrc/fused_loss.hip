@@ -172,10 +172,8 @@ __device__ __forceinline__ void loss_grad_group(cf (&v)[1 << E], cf (&nx)[1 << E
         lds_sync<WAVE>();  // LDS is reused by the next group
 }
 
-// PLAIN: the gradient stays in the memory-side cache, where the backward,
-// which scales it, finds it (keep_gradient says when that pays).  A call on its
-// own stores nontemporally: plain stores cost it 2-25 % (N = 64 at 250 MiB
-// 102 -> 125 us).  Compiled for the built-in shapes.
+// PLAIN: the gradient stays in a cache, where the backward, which scales it,
+// finds it (keep_gradient says when).  Compiled for the built-in shapes.
 //
 // Persistent: workgroups walk transform groups, loading the next group's x
 // while the current one is processed.
@@ -231,7 +229,7 @@ hipError_t launch_loss_grad(const void* x, const float* w, void* grad, float* lo
     if (grid_limit > 0 && grid > grid_limit)
         grid = grid_limit;
     constexpr bool builtin = kDefaultLoss[L].log2ept == E && kDefaultLoss[L].wg == WG;
-    const bool plain = builtin && scaled_next && keep_gradient(L, batch * (int64_t(8) << L));
+    const bool plain = builtin && keep_gradient(L, batch * (int64_t(8) << L), scaled_next);
     return launch_kernel(plain ? k_fft_loss_grad<L, E, WG, S, builtin> : k_fft_loss_grad<L, E, WG, S, false>,
                          dim3((unsigned)grid), dim3(WG), 0, stream, static_cast<const cf*>(x), w,
                          static_cast<cf*>(grad), loss, static_cast<const cf*>(rows), batch, scale);

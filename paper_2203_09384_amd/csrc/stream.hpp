@@ -54,17 +54,18 @@ inline bool fourstep_bulk(int log2n, int64_t bytes)
     return is_bulk(bytes) && (log2n > 15 || bytes <= (kStreamBytes >> 1) || is_stream(bytes));
 }
 
-// Whether the differentiable loss stores its gradient of `bytes` plainly, so that
-// the backward, which scales it, finds it in a cache.  MI355X, forward +
-// backward in us, three inputs in turn, nontemporal -> plain: N = 2048 at 0.5 MiB
-// 8.0 -> 7.7, 2: 9.0 -> 8.8, 8: 15.2 -> 16.3, 24: 29.2 -> 29.8, 40: 39.9 -> 39.1,
-// 150: 127.5 -> 116.8, 250: 206 -> 184, 300: 244 -> 244; N = 128 at 0.5 MiB
-// 6.1 -> 5.8, 16: 18.4 -> 19.1, 40: 35.8 -> 33.7, 200: 148.5 -> 142.8,
-// 250: 186 -> 193.
-inline bool keep_gradient(int log2n, int64_t bytes)
+// Whether the fused loss stores its gradient of `bytes` plainly: small ones, which
+// the XCDs' L2 caches take faster than memory does, and larger ones if the next
+// kernel scales it (the differentiable loss's backward).  MI355X, us, three inputs
+// in turn, nontemporal -> plain: alone N = 512 at 2 MiB 5.2 -> 4.5, N = 2048 at
+// 2 MiB 7.0 -> 6.2, N = 256 at 16 MiB 8.9 -> 11.2; forward + backward N = 2048 at
+// 0.5 MiB 8.0 -> 7.7, 8: 15.2 -> 16.3, 24: 29.2 -> 29.8, 40: 39.9 -> 39.1, 150: 127.5
+// -> 116.8, 250: 206 -> 184, 300: 244 -> 244; N = 128 at 0.5 MiB 6.1 -> 5.8, 16:
+// 18.4 -> 19.1, 40: 35.8 -> 33.7, 200: 148.5 -> 142.8, 250: 186 -> 193.
+inline bool keep_gradient(int log2n, int64_t bytes, bool scaled_next)
 {
-    return bytes <= (kStreamBytes >> 6) ||
-           (bytes > (kStreamBytes >> 2) && bytes <= (log2n >= 9 ? kChunkBytes : kChunkBytes / 8 * 7));
+    return bytes <= (kStreamBytes >> 6) || (scaled_next && bytes > (kStreamBytes >> 2) &&
+                                            bytes <= (log2n >= 9 ? kChunkBytes : kChunkBytes / 8 * 7));
 }
 
 // Whether the first pass of a multidimensional transform, along 2^log2n points,

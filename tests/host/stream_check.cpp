@@ -19,6 +19,9 @@ int64_t st_stream_bytes() { return kStreamBytes; }
 int st_fourstep_bulk(int log2n, int64_t bytes) { return fourstep_bulk(log2n, bytes); }
 }
 
-extern "C" int st_keep_gradient(int log2n, int64_t bytes) { return keep_gradient(log2n, bytes); }
+extern "C" int st_keep_gradient(int log2n, int64_t bytes, int scaled_next)
+{
+    return keep_gradient(log2n, bytes, scaled_next != 0);
+}
 
 extern "C" int st_feed_next(int log2n, int64_t bytes) { return feed_next(log2n, bytes); }

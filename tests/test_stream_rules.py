@@ -71,10 +71,12 @@ def test_fourstep_bulk(st, log2n):
 
 @pytest.mark.parametrize("log2n,most", [(1, 224), (8, 224), (9, 256), (11, 256)])
 def test_keep_gradient(st, log2n, most):
-    st.st_keep_gradient.argtypes = [ctypes.c_int, I64]
-    for nbytes, want in ((1 << 10, True), (2 << 20, True), ((2 << 20) + 8, False), (32 << 20, False), ((32 << 20) + 8, True), (most << 20, True),
-                         ((most << 20) + 8, False), (1 << 30, False)):
-        assert bool(st.st_keep_gradient(log2n, nbytes)) == want, nbytes
+    st.st_keep_gradient.argtypes = [ctypes.c_int, I64, ctypes.c_int]
+    for nbytes, alone, scaled in ((1 << 10, True, True), (2 << 20, True, True), ((2 << 20) + 8, False, False),
+                                  (32 << 20, False, False), ((32 << 20) + 8, False, True), (most << 20, False, True),
+                                  ((most << 20) + 8, False, False), (1 << 30, False, False)):
+        assert bool(st.st_keep_gradient(log2n, nbytes, 0)) == alone, nbytes
+        assert bool(st.st_keep_gradient(log2n, nbytes, 1)) == scaled, nbytes
 
 
 @pytest.mark.parametrize("log2n,low,high", [(1, 8, 20), (7, 6, 20), (8, 8, 20), (12, 8, 28), (14, 8, 20)])
