@@ -136,14 +136,17 @@ typedef struct {
  *          LDS); 2^15 .. 2^20 (the paper's future work, section
  *          "Conclusions") use the four-step split N = N1 N2: a column pass
  *          with the w_N^{n2 k1} twiddles, then an in-place row pass in
- *          `out` (two kernels on the stream per 256 MiB of input).  FFT_C16 / FFT_CBF16: [2, 2048]
+ *          `out` (two kernels on the stream per 256 MiB of input).
+ *          FFT_C16 / FFT_CBF16: [2, 2048]
  *          (2048: radix-16 passes on MFMA; below: the FP32 passes with
  *          16-bit storage).
  *          FFT_R32: [2, 2^21]; up to 2^15 one fused kernel per
  *          execute, above it the half-length four-step transform with the
- *          split folded into its passes, through a plan-owned workspace of
- *          n/2 complex values per transform, at most 128 MiB (allocated
- *          here; executes of one such plan must not overlap in time).
+ *          split folded into its passes.  Reals to bins (the execute of a
+ *          forward plan, the adjoint of an inverse one) go through a
+ *          plan-owned workspace of n/2 complex values per transform, at most
+ *          128 MiB (or one transform's), allocated here: such calls of one
+ *          plan must not overlap in time.  Bins to reals use none.
  *   batch  >= 1.
  *   sign   -1: forward transform Eq. (dft), scale 1.
  *          +1: inverse transform Eq. (idft), scale 1/n.
@@ -154,7 +157,9 @@ typedef struct {
  * table (blocking, on the legacy default stream).  Returns NULL on error;
  * see fft_last_error().  The kernel variant (elements per thread and
  * workgroup size) comes from the built-in tuned table, or from the file
- * named by the environment variable MIFFT_TUNE_TABLE if set.
+ * named by the environment variable MIFFT_TUNE_TABLE if set.  The built-in
+ * choice depends on the size of the call; an entry of the file holds for
+ * calls of every size, also below the sizes that the tuner measures.
  * Plan creation (this and every other fft_plan_create_* call) allocates and
  * synchronises, so it must not run while a stream capture is active: it
  * returns NULL with FFT_ECAPTURE when HIP reports one.  Create plans before
@@ -250,12 +255,13 @@ int fft_execute(fft_plan p, const void *in, void *out, void *stream);
  * while they execute (code under stream capture, tight serving loops,
  * harnesses that forbid allocation): fft_execute with every intermediate in
  * memory the library already holds.  Allocates nothing and frees nothing.
- *   FFT_R32 plans above 2^15 (the half-length four-step transform with the
- *   split): the intermediate spectrum of n/2 complex values per
+ *   Forward FFT_R32 plans above 2^15 (the half-length four-step transform
+ *   with the split): the intermediate spectrum of n/2 complex values per
  *   transform goes to a static scratch array of MIFFT_STATIC_SCRATCH_BYTES
  *   per GPU instead of the plan's workspace, so (n/2) * batch * 8 bytes must
  *   fit: FFT_EINVAL_BATCH otherwise, with the largest batch for that length
- *   in the message (e.g. 256 transforms of 2^16 reals, 8 of 2^21).
+ *   in the message (e.g. 256 transforms of 2^16 reals, 8 of 2^21).  Inverse
+ *   plans above 2^15 need no scratch but keep the same limit.
  *   Every other plan: exactly fft_execute (those executes use no workspace).
  * Arguments, layouts, sizes and error codes otherwise as fft_execute.
  * The scratch array's device address is looked up on the first call on each

@@ -347,8 +347,8 @@ struct mifft_plan_s {
     const KernelReal* r2c = nullptr;  // FFT_R32: real -> bins kernel
     const KernelReal* c2r = nullptr;  // FFT_R32: bins -> real kernel
     void* wn = nullptr;               // FFT_R32: w_n^k, k < n/2
-    // FFT_R32 above 2^15: four-step half-length sub-plan, its workspace
-    // (n/2 complex per transform) and the two-level w_n table of the split
+    // FFT_R32 above 2^15: four-step half-length sub-plan, R2C's workspace (n/2
+    // complex per transform of a chunk) and the two-level w_n table of the split
     mifft_plan_s* real_sub = nullptr;
     void* real_ws = nullptr;
     void* real_tw = nullptr;
@@ -1220,7 +1220,7 @@ int check_exec(fft_plan p, const void* in, const void* out, bool to_bins = false
 }
 
 // FFT_R32: to_bins selects the real -> bins kernel; we / wi weight the
-// edge and interior bins (see real.hip).  ws: the workspace of a plan above
+// edge and interior bins (see real.hip).  ws: the workspace of an R2C above
 // 2^15 (n/2 complex values per transform), NULL for the plan's own.
 int exec_real(fft_plan p, const void* in, void* out, bool to_bins, float we, float wi, hipStream_t st,
               void* ws = nullptr)

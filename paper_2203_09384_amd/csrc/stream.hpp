@@ -1,7 +1,7 @@
 // How passes over memory use MI355X's 256 MiB memory-side cache.
 //
 // Nontemporal accesses leave the cache to other data; plain ones fill it.
-// Two rules, on the bytes that one direction of a call moves:
+// The rules go by the bytes that one direction of a call moves:
 //
 // - Streams.  A call whose input and output together exceed the cache can
 //   find its input there only by accident, and filling it with data that is
@@ -10,8 +10,8 @@
 //   next one reads its output, at the cache's rate: plain accesses.
 //   Measured with 16-column tile copies: 2 x 64 MiB, repeated on the same
 //   buffers, 17 us plain against 23 nontemporal; 2 x 512 MiB 205 against 189.
-// - One pass.  A transform of a single pass reads and stores nontemporally at
-//   every size.  Plain stores leave an output of up to 256 MiB in the cache,
+// - One pass.  Batched 1D transforms of a single pass read and store
+//   nontemporally at every size.  Plain stores leave an output of up to 256 MiB in the cache,
 //   which helps a program that writes one buffer again and again or whose
 //   next kernel works on the output in place, and costs the others what
 //   the output drives out: N = 64 at 128 MiB, nontemporal -> plain stores, three
@@ -36,8 +36,9 @@ constexpr int64_t kChunkBytes = int64_t(256) << 20;
 // calls that fill the chip several times over, for the loads in flight; in
 // smaller ones 8 or 16 points per thread make four or two times the
 // wavefronts.  MI355X, 8 / 16 -> 32 points per thread, us: four-step 2^16 at
-// 64 MiB 51.0 -> 43.0, at 512 MiB 349 -> 346, at 16 MiB 22.6 -> 23.3, at 2 MiB
-// 10.9 -> 12.0; 2D 256 x 256 at 64 MiB 49.2 -> 44.3.
+// 64 MiB 51.0 -> 43.0 (three buffer sets in turn 55.9 -> 58.1, at 56 MiB 49.0 ->
+// 44.2), at 512 MiB 349 -> 346, at 16 MiB 22.6 -> 23.3, at 2 MiB 10.9 -> 12.0; 2D
+// 256 x 256 at 64 MiB 49.2 -> 44.3.
 constexpr int64_t kBulkBytes = int64_t(32) << 20;
 inline bool is_bulk(int64_t bytes) { return bytes > kBulkBytes; }
 
